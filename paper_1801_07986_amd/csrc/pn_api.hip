@@ -132,7 +132,7 @@ int pick_stage_ns(int64_t N, int precision) {
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 struct Layout {
-  size_t pk, ub, bpart, ub2, bpart2, bhpart2, part, bhpart, status, xs, vs, kx, kv, dpart, out8, ha, hj, xp, vp, ap,
+  size_t pk, ub, bpart, ub2, bpart2, bhpart2, part, bhpart, status, xs, vs, kx, kv, ha, hj, xp, vp, ap,
       pk2, bpart3, bpart4, bhs, total;
 };
 
@@ -172,7 +172,7 @@ Layout layout_for(int64_t N, const Shape& s, Need need, int stage_ns = 0) {
   L.bpart = take(nrows * 8 * W * sizeof(double));
   L.ub2 = take(rk4 || dual ? Ns * 4 * W * sizeof(double) : 0);
   L.bpart2 = take(rk4 || dual ? nrows * 8 * W * sizeof(double) : 0);
-  L.part = take((size_t)s.nsplit * std::max<size_t>(kNF * W, kND) * Ns * sizeof(double));
+  L.part = take((size_t)s.nsplit * kNF * W * Ns * sizeof(double));
   L.bhpart = take(nepi * 4 * W * sizeof(double));
   L.bhpart2 = take(dual || fused ? nepi * 4 * W * sizeof(double) : 0);
   L.pk2 = take(fused ? Ns * sizeof(PkF64) : 0);
@@ -180,8 +180,6 @@ Layout layout_for(int64_t N, const Shape& s, Need need, int stage_ns = 0) {
   L.bpart4 = take(fused ? nbf * 8 * sizeof(double) : 0);
   L.bhs = take(fused ? 36 * sizeof(double) : 0);
   L.status = take(sizeof(int));
-  L.dpart = take(nb * 10 * sizeof(double));
-  L.out8 = take(8 * sizeof(double));
   const size_t n3 = 3 * (size_t)N * sizeof(double);
   L.xs = take(rk4 ? n3 : 0);
   L.vs = take(rk4 ? n3 : 0);
@@ -193,6 +191,38 @@ Layout layout_for(int64_t N, const Shape& s, Need need, int stage_ns = 0) {
   L.vp = take(herm ? n3 : 0);
   L.ap = take(herm ? n3 : 0);
   L.total = o;
+  return L;
+}
+
+// Grid and scratch of the pair sweeps over i < j (diagnostics, encounters):
+// i-blocks of kBlock stars x j-chunks.  About 8192 workgroups have pairs (half
+// of the grid): with 2048 the N = 65536 sweep takes 3.5 ms instead of 2.85,
+// its last round of workgroups being nearly empty.  A chunk keeps at least 16
+// j (where launches are all that counts: 42.8 us a call at N = 100 against 52
+// with 64), 64 from N = 4096 on (N = 10001: 127 us against 136 with 32, whose
+// rows the last kernel sums).
+struct TriPlan {
+  int nb, nchunk, jchunk;
+};
+TriPlan tri_plan(int Ns) {
+  TriPlan T;
+  T.nb = (Ns + kBlock - 1) / kBlock;
+  const int least = std::max(16, std::min(64, Ns / 64));
+  const int want = std::max(1, std::min(2 * 8192 / T.nb, (Ns + least - 1) / least));
+  T.jchunk = (Ns + want - 1) / want;
+  T.nchunk = (Ns + T.jchunk - 1) / T.jchunk;
+  return T;
+}
+struct TriLayout {
+  size_t pk, srow, prow, out, total;
+};
+TriLayout tri_layout(const TriPlan& T, int Ns, size_t packet) {
+  TriLayout L;
+  L.pk = 0;
+  L.srow = align256(packet * Ns);
+  L.prow = L.srow + align256((size_t)T.nb * 10 * sizeof(double));
+  L.out = L.prow + align256((size_t)T.nb * T.nchunk * kTriRow * sizeof(double));
+  L.total = L.out + align256(9 * sizeof(double));
   return L;
 }
 
@@ -1531,45 +1561,41 @@ int pn_diagnostics(const double* pos, const double* vel, const double* mass, int
   std::lock_guard<std::mutex> lk(g_mu);
   DevState* d;
   if ((rc = dev_state(&d))) return rc;
-  const Shape sh = pick_shape((int)(N - 1), PN_FP64);
-  const Layout L = layout_for(N, sh, Need::EVAL);
+  const int Ns = (int)(N - 1);
+  const TriPlan T = tri_plan(Ns);
+  const TriLayout L = tri_layout(T, Ns, sizeof(PkDiag));
   if ((rc = ensure_scratch(*d, L.total))) return rc;
-  Ptrs P{d->base, L};
+  char* base = d->base;
   hipStream_t st = pick_stream(*d, stream);
   if ((rc = order_after_previous(*d, st))) return rc;
-  Sys s{pos, vel, mass, N, G, c, eps};
-  if ((rc = reset_status(P, st))) return rc;
-  if ((rc = launch_prologue(s, P, PN_FP64, st))) return rc;
-  const int Ns = (int)(N - 1);
-  const int nb = (Ns + kBlock - 1) / kBlock;
-  DiagPairArgs dp;
-  dp.pk = P.at<PkF64>(L.pk);
-  dp.Ns = Ns;
-  dp.jchunk = sh.jchunk;
-  dp.eps2 = eps * eps;
-  dp.part = P.at<double>(L.part);
-  hipLaunchKernelGGL(k_diag_pair, dim3(nb, sh.nsplit), dim3(kBlock), 0, st, dp);
+  DiagArgs a;
+  a.pos = pos;
+  a.vel = vel;
+  a.mass = mass;
+  a.Ns = Ns;
+  a.G = G;
+  a.lam = lambda_of(c);
+  a.eps2 = eps * eps;
+  a.pk = reinterpret_cast<PkDiag*>(base + L.pk);
+  a.srow = reinterpret_cast<double*>(base + L.srow);
+  a.nsrow = T.nb;
+  a.prow = reinterpret_cast<double*>(base + L.prow);
+  a.nprow = T.nb * T.nchunk;
+  a.out = reinterpret_cast<double*>(base + L.out);
+  const TriArgs t{Ns, T.jchunk, a.eps2, a.prow};
+  hipLaunchKernelGGL(k_diag_stars, dim3(T.nb), dim3(kBlock), 0, st, a);
   HIPCK(hipGetLastError());
-  DiagEpiArgs de;
-  de.pos = pos;
-  de.vel = vel;
-  de.mass = mass;
-  de.Ns = Ns;
-  de.G = G;
-  de.lam = lambda_of(c);
-  de.eps2 = eps * eps;
-  de.ub = P.at<double>(L.ub);
-  de.part = P.at<double>(L.part);
-  de.nsplit = sh.nsplit;
-  de.dpart = P.at<double>(L.dpart);
-  de.ndpart = nb;
-  de.out8 = P.at<double>(L.out8);
-  hipLaunchKernelGGL(k_diag_epi, dim3(nb), dim3(kBlock), 0, st, de);
+  hipLaunchKernelGGL(k_diag_pair, dim3(T.nb, T.nchunk), dim3(kBlock), 0, st, t, a.pk, mass);
   HIPCK(hipGetLastError());
-  hipLaunchKernelGGL(k_diag_final, dim3(1), dim3(kBlock), 0, st, de);
+  hipLaunchKernelGGL(k_diag_final, dim3(1), dim3(kTriFinal), 0, st, a);
   HIPCK(hipGetLastError());
-  HIPCK(hipMemcpyAsync(out8, P.at<double>(L.out8), 8 * sizeof(double), hipMemcpyDeviceToHost, st));
-  return finish(*d, P, st, 0);
+  double got[9];  // the results and the status, one copy
+  HIPCK(hipMemcpyAsync(got, a.out, sizeof got, hipMemcpyDeviceToHost, st));
+  if ((rc = mark_call_end(*d, st))) return rc;
+  HIPCK(hipStreamSynchronize(st));
+  memcpy(out8, got, 8 * sizeof(double));
+  if (got[8] != 0.0) return fail_inval("mass[0] must be positive and finite");
+  return PN_OK;
 }
 
 int pn_encounters(const double* pos, const double* vel, const double* mass, int64_t N, double G,
@@ -1585,45 +1611,34 @@ int pn_encounters(const double* pos, const double* vel, const double* mass, int6
   int rc = dev_state(&d);
   if (rc) return rc;
   const int Ns = (int)(N - 1);
-  const int nb = (Ns + kBlock - 1) / kBlock;
-  Shape sh = pick_shape(Ns, PN_FP64);
-  const int nsplit = std::max(1, std::min(sh.nsplit * 4, std::max(1, Ns / 64)));
-  const int jchunk = (Ns + nsplit - 1) / nsplit;
-  const int ns = (Ns + jchunk - 1) / jchunk;
-  Shape s2 = sh;
-  s2.nsplit = std::max(sh.nsplit, ns);  // scratch for the larger split count
-  Layout L = layout_for(N, s2, Need::EVAL);
-  const size_t extra = align256((size_t)nb * 2 * sizeof(long long));
-  if ((rc = ensure_scratch(*d, L.total + extra))) return rc;
-  Ptrs P{d->base, L};
+  const TriPlan T = tri_plan(Ns);
+  const TriLayout L = tri_layout(T, Ns, sizeof(double4));
+  if ((rc = ensure_scratch(*d, L.total))) return rc;
+  char* base = d->base;
   hipStream_t st = pick_stream(*d, stream);
   if ((rc = order_after_previous(*d, st))) return rc;
-  Sys sys{pos, nullptr, mass, N, 1.0, 1.0, 0.0};
-  if ((rc = reset_status(P, st))) return rc;
-  if ((rc = launch_prologue(sys, P, PN_FP64, st))) return rc;  // packets hold the positions
   EncArgs e;
   e.pos = pos;
   e.vel = vel;
   e.mass = mass;
+  e.Ns = Ns;
+  e.r_close2 = r_close * r_close;
   e.G = G;
   e.lam = lambda_of(c);
-  e.pk = P.at<PkF64>(L.pk);
-  e.Ns = Ns;
-  e.jchunk = jchunk;
-  e.r_close2 = r_close * r_close;
-  e.part = P.at<double>(L.part);
-  e.nsplit = ns;
-  e.bpart = P.at<double>(L.dpart);
-  e.bpair = reinterpret_cast<long long*>(d->base + L.total);
-  e.nb = nb;
-  e.out = P.at<double>(L.out8);
-  hipLaunchKernelGGL(k_enc_pair, dim3(nb, ns), dim3(kBlock), 0, st, e);
+  e.pk = reinterpret_cast<double4*>(base + L.pk);
+  e.srow = reinterpret_cast<double*>(base + L.srow);
+  e.nsrow = T.nb;
+  e.prow = reinterpret_cast<double*>(base + L.prow);
+  e.nprow = T.nb * T.nchunk;
+  e.out = reinterpret_cast<double*>(base + L.out);
+  const TriArgs t{Ns, T.jchunk, 0.0, e.prow};
+  hipLaunchKernelGGL(k_enc_stars, dim3(T.nb), dim3(kBlock), 0, st, e);
   HIPCK(hipGetLastError());
-  hipLaunchKernelGGL(k_enc_star, dim3(nb), dim3(kBlock), 0, st, e);
+  hipLaunchKernelGGL(k_enc_pair, dim3(T.nb, T.nchunk), dim3(kBlock), 0, st, t, e.pk);
   HIPCK(hipGetLastError());
-  hipLaunchKernelGGL(k_enc_final, dim3(1), dim3(64), 0, st, e);
+  hipLaunchKernelGGL(k_enc_final, dim3(1), dim3(kTriFinal), 0, st, e);
   HIPCK(hipGetLastError());
-  HIPCK(hipMemcpyAsync(out8, P.at<double>(L.out8), 8 * sizeof(double), hipMemcpyDeviceToHost, st));
+  HIPCK(hipMemcpyAsync(out8, e.out, 8 * sizeof(double), hipMemcpyDeviceToHost, st));
   if ((rc = mark_call_end(*d, st))) return rc;
   HIPCK(hipStreamSynchronize(st));
   return PN_OK;

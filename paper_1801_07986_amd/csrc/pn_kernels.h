@@ -254,22 +254,6 @@ __device__ __forceinline__ void clear_pad(PkF64& p) { p.pad = 0.0; }
 __device__ __forceinline__ void clear_pad(PkF32& p) { p.pad0 = p.pad1 = 0.f; }
 __device__ __forceinline__ void clear_pad(PkDual&) {}
 
-// Fixed-order workgroup sum of K doubles per thread; result in lds[k*kBlock].
-template <int K>
-__device__ __forceinline__ void block_sum(const double (&v)[K], double* lds) {
-  const int t = threadIdx.x;
-#pragma unroll
-  for (int k = 0; k < K; ++k) lds[k * kBlock + t] = v[k];
-  __syncthreads();
-  for (int s = kBlock / 2; s > 0; s >>= 1) {
-    if (t < s) {
-#pragma unroll
-      for (int k = 0; k < K; ++k) lds[k * kBlock + t] += lds[k * kBlock + t + s];
-    }
-    __syncthreads();
-  }
-}
-
 // A double from another lane of the same row of 16 by a DPP move (two 32-bit
 // halves); CTRL: 0x141 lane i <- 7 - i within 8, 0x140 i <- 15 - i within 16,
 // 0xB1 / 0x4E (quad permutations) i <- i ^ 1 / i ^ 2.
@@ -1598,140 +1582,208 @@ __global__ __launch_bounds__(kBlock) void k_stage_head(EpiArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// Diagnostics (Eqs. (7)-(8)).  Star-star pair sums per star i:
-//   U_i = sum_j G m_j / R_ij
-//   W_i = sum_j (G m_j / R_ij) [-7 v_i.v_j - (n_ij.v_i)(n_ij.v_j)]
-//   Y_i = sum_j (G m_j / R_ij) (v_i.n_ij) n_ij
-// then O(N) terms per star and fixed-order reductions.
+// Diagnostics (Eqs. (7)-(8)) and close encounters.  Both need sums (minima)
+// over all star pairs only, and every pair term is symmetric, so a pair is
+// visited once: lane i takes the j > i.  The grid is (i-blocks of kBlock
+// stars) x (j-chunks); a chunk that ends at or before its block's first star
+// has no pair and writes an empty row.  Each workgroup reduces its lanes and writes
+// one row, a last workgroup sums the rows in fixed order: three kernels, and
+// no per-star partial sums in memory.
+//
+// The sweeps are bound by vector issue: per unordered pair 37 operations and
+// one reciprocal square root (diagnostics), 8 operations (encounters, four j at
+// a time).  Forms with a sum (minimum) per star took 39 and 11 per ordered
+// pair.  At N = 10001 the diagnostics' sweep takes 90 us (250 per ordered
+// pair), the encounters' 28 (92), and their stars' and last kernels 21 (44,
+// by LDS trees and one serial thread); a record (both calls) 188 us (478).
 // ---------------------------------------------------------------------------
-constexpr int kND = 5;  // U, W, Y(3)
-
-struct DiagPairArgs {
-  const PkF64* pk;
+struct TriArgs {
   int Ns, jchunk;
   double eps2;
-  double* part;  // [gridDim.y][kND][Ns]
+  double* rows;  // [gridDim.y][gridDim.x][kTriRow]
 };
+constexpr int kTriRow = 8;       // doubles per row
+constexpr int kTriFinal = 1024;  // threads of the workgroup that sums the rows
 
-__global__ __launch_bounds__(kBlock) void k_diag_pair(DiagPairArgs a) {
-  const PkF64* __restrict__ pk = a.pk;
+__device__ __forceinline__ bool tri_live(int block, int chunk, int jchunk) {
+  return ((int64_t)chunk + 1) * jchunk > (int64_t)block * kBlock;
+}
+
+// The pairs of lane i in its workgroup's chunk, from the block's first star
+// on: one(j) where j may be <= i, four(j) for the four stars j .. j + 3 beyond
+// the block, last(j) for what is left of them.
+template <typename One, typename Four, typename Last>
+__device__ __forceinline__ void tri_range(const TriArgs& a, One&& one, Four&& four, Last&& last) {
   const int ilo = blockIdx.x * kBlock;
-  const int ihi = min(a.Ns, ilo + kBlock);
-  const int i = ilo + threadIdx.x;
-  const PkF64& pi = pk[min(i, a.Ns - 1)];
-  const double xi = pi.x, yi = pi.y, zi = pi.z;
-  constexpr double iv = PairScale<double>::inv_sv;
-  const double vxi = iv * pi.svx, vyi = iv * pi.svy, vzi = iv * pi.svz;
-  const int j0 = blockIdx.y * a.jchunk, j1 = min(a.Ns, j0 + a.jchunk);
-  double U = 0.0, W = 0.0, Yx = 0.0, Yy = 0.0, Yz = 0.0;
-  for (int j = j0; j < j1; ++j) {
-    const PkF64& p = pk[j];
-    const double dx = xi - p.x, dy = yi - p.y, dz = zi - p.z;
-    double rinv = rsqrt_f64(fma(dz, dz, fma(dy, dy, fma(dx, dx, a.eps2))));
-    if (j >= ilo && j < ihi) rinv = (j == i) ? 0.0 : rinv;
-    const double mr = p.gm * rinv;
-    const double rinv2 = rinv * rinv;
-    const double vxj = iv * p.svx, vyj = iv * p.svy, vzj = iv * p.svz;
-    const double vv = fma(vzi, vzj, fma(vyi, vyj, vxi * vxj));
-    const double xvi = fma(dz, vzi, fma(dy, vyi, dx * vxi));
-    const double xvj = fma(dz, vzj, fma(dy, vyj, dx * vxj));
-    U += mr;
-    W = fma(mr, fma(-xvi * xvj, rinv2, -7.0 * vv), W);
-    const double cy = mr * xvi * rinv2;
-    Yx = fma(cy, dx, Yx);
-    Yy = fma(cy, dy, Yy);
-    Yz = fma(cy, dz, Yz);
-  }
-  if (i < a.Ns) {
-    const size_t plane = (size_t)a.Ns;
-    double* out = a.part + (size_t)blockIdx.y * kND * plane + i;
-    out[0] = U;
-    out[plane] = W;
-    out[2 * plane] = Yx;
-    out[3 * plane] = Yy;
-    out[4 * plane] = Yz;
+  const int j0 = max((int)blockIdx.y * a.jchunk, ilo);
+  const int j1 = (int)min((int64_t)a.Ns, ((int64_t)blockIdx.y + 1) * a.jchunk);
+  const int jm = min(j1, ilo + kBlock);
+  int j = j0;
+  for (; j < jm; ++j) one(j);
+  for (; j + 3 < j1; j += 4) four(j);
+  for (; j < j1; ++j) last(j);
+}
+
+// Sums over the workgroup of K doubles per thread, in every thread of its first
+// wavefront: wavefront butterflies, then the wavefronts in order.
+template <int K>
+__device__ __forceinline__ void group_sum(double (&v)[K], double* lds) {
+  wave_allsum<K>(v);
+  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+  if (l < K) lds[w * K + l] = pick(v, l);
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < K; ++k) v[k] = lds[k];
+  for (int u = 1; u < (int)(blockDim.x >> 6); ++u) {
+#pragma unroll
+    for (int k = 0; k < K; ++k) v[k] += lds[u * K + k];
   }
 }
 
-struct DiagEpiArgs {
+// Star packet of the diagnostics: q = 3/2 v^2 + u.
+struct alignas(64) PkDiag {
+  double x, y, z, gm, vx, vy, vz, q;
+};
+
+struct DiagArgs {
   const double* pos;
   const double* vel;
   const double* mass;
   int Ns;
   double G, lam, eps2;
-  const double* ub;
-  const double* part;
-  int nsplit;
-  double* dpart;  // [gridDim.x][10]
-  int ndpart;     // (k_diag_final) rows of dpart
-  double* out8;   // (k_diag_final)
+  PkDiag* pk;
+  double* srow;  // [star blocks][10]: sums of the stars' own terms
+  int nsrow;
+  double* prow;  // pair rows (TriArgs::rows)
+  int nprow;
+  double* out;   // [9]: the eight results, then the status
 };
 
-// Per-star contributions, columns of dpart:
-//  0: 1/2 m v^2 - 1/2 m U - m u          (Newtonian energy, stars)
-//  1: 1PN energy bracket, star terms
+// The stars' own terms (columns of srow) and their packets.
+//  0: 1/2 m v^2 - m u                     (Newtonian energy, stars)
+//  1: 1PN energy bracket without star-star pairs
 //  2: m u / M  (sum = U0 = sum_i G m_i / R_1i)
 //  3-5: m v                               (Newtonian momentum, stars)
-//  6-8: 1PN momentum bracket, star terms
-__global__ __launch_bounds__(kBlock) void k_diag_epi(DiagEpiArgs a) {
-  __shared__ double lds[9 * kBlock];
+//  6-8: 1PN momentum bracket without star-star pairs
+__global__ __launch_bounds__(kBlock) void k_diag_stars(DiagArgs a) {
+  __shared__ double lds[9 * kBlock / 64];
   const int k = blockIdx.x * kBlock + threadIdx.x;
   double v[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
   if (k < a.Ns) {
     const int i = k + 1;
-    const size_t plane = (size_t)a.Ns;
-    double U = 0.0, W = 0.0, Y[3] = {0.0, 0.0, 0.0};
-    for (int sp = 0; sp < a.nsplit; ++sp) {
-      const double* pp = a.part + (size_t)sp * kND * plane + k;
-      U += pp[0];
-      W += pp[plane];
-      Y[0] += pp[2 * plane];
-      Y[1] += pp[3 * plane];
-      Y[2] += pp[4 * plane];
-    }
     const double M = a.mass[0], m = a.mass[i];
-    const double u = a.ub[4 * (size_t)k];
-    const double* vi = a.vel + 3 * i;
+    const double* vi = a.vel + 3 * (size_t)i;
     const double* v1 = a.vel;
-    const double d[3] = {a.pos[0] - a.pos[3 * i], a.pos[1] - a.pos[3 * i + 1],
-                         a.pos[2] - a.pos[3 * i + 2]};  // x_1i
-    const double rinv = rsqrt_f64(d[0] * d[0] + d[1] * d[1] + d[2] * d[2] + a.eps2);
+    const double* xi = a.pos + 3 * (size_t)i;
+    const double d[3] = {a.pos[0] - xi[0], a.pos[1] - xi[1], a.pos[2] - xi[2]};  // x_1i
+    const double rinv = rsqrt_f64(fma(d[2], d[2], fma(d[1], d[1], fma(d[0], d[0], a.eps2))));
+    const double u = a.G * M * rinv;
     const double n[3] = {d[0] * rinv, d[1] * rinv, d[2] * rinv};
     const double vi2 = vi[0] * vi[0] + vi[1] * vi[1] + vi[2] * vi[2];
     const double v12 = v1[0] * v1[0] + v1[1] * v1[1] + v1[2] * v1[2];
     const double v1vi = v1[0] * vi[0] + v1[1] * vi[1] + v1[2] * vi[2];
     const double nv1 = n[0] * v1[0] + n[1] * v1[1] + n[2] * v1[2];
     const double nvi = n[0] * vi[0] + n[1] * vi[1] + n[2] * vi[2];
-    v[0] = 0.5 * m * vi2 - 0.5 * m * U - m * u;
+    a.pk[k] = PkDiag{xi[0], xi[1], xi[2], a.G * m, vi[0], vi[1], vi[2], fma(1.5, vi2, u)};
+    v[0] = 0.5 * m * vi2 - m * u;
     v[1] = 0.375 * m * vi2 * vi2 + 1.5 * m * u * vi2 + 0.5 * m * u * u +
-           0.25 * m * (6.0 * vi2 * U + W) + 0.5 * m * u * (3.0 * v12 - 7.0 * v1vi - nv1 * nvi) +
-           m * u * U;
+           0.5 * m * u * (3.0 * v12 - 7.0 * v1vi - nv1 * nvi);
     v[2] = m * u / M;
     for (int c = 0; c < 3; ++c) {
       v[3 + c] = m * vi[c];
       v[6 + c] = 0.5 * m * vi2 * vi[c] - 0.5 * m * u * (vi[c] + nvi * n[c]) -
-                 0.5 * m * u * (v1[c] + nv1 * n[c]) - 0.5 * m * (U * vi[c] + Y[c]);
+                 0.5 * m * u * (v1[c] + nv1 * n[c]);
     }
   }
-  block_sum<9>(v, lds);
-  if (threadIdx.x < 10)
-    a.dpart[(size_t)blockIdx.x * 10 + threadIdx.x] = threadIdx.x < 9 ? lds[threadIdx.x * kBlock] : 0.0;
+  group_sum<9>(v, lds);
+  if (threadIdx.x < 9) a.srow[(size_t)blockIdx.x * 10 + threadIdx.x] = pick(v, threadIdx.x);
 }
 
-__global__ __launch_bounds__(kBlock) void k_diag_final(DiagEpiArgs a) {
-  double r[9];
-  reduce_rows<9>(a.dpart, a.ndpart, 10, r);
+// Star pairs, p = G m_i m_j / R, n = x_ij / R: columns of a row
+//  0: -sum p                                        (Newtonian energy)
+//  1: sum p [q_i + q_j - 7/2 v_i.v_j - 1/2 (n.v_i)(n.v_j)]   (1PN energy)
+//  2-4: -1/2 sum p [(v_i + v_j) + (n.(v_i + v_j)) n]         (1PN momentum)
+__global__ __launch_bounds__(kBlock) void k_diag_pair(TriArgs a,
+                                                     const PkDiag* __restrict__ pk,
+                                                     const double* __restrict__ mass) {
+  __shared__ double lds[5 * kBlock / 64];
+  double* row = a.rows + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * kTriRow;
+  if (!tri_live(blockIdx.x, blockIdx.y, a.jchunk)) {
+    if (threadIdx.x < 5) row[threadIdx.x] = 0.0;
+    return;
+  }
+  const int i = blockIdx.x * kBlock + threadIdx.x;
+  const PkDiag I = pk[min(i, a.Ns - 1)];
+  const double hx = -3.5 * I.vx, hy = -3.5 * I.vy, hz = -3.5 * I.vz;
+  double s0 = 0.0, s1 = 0.0, vx = 0.0, vy = 0.0, vz = 0.0, yx = 0.0, yy = 0.0, yz = 0.0;
+  auto pair = [&](const PkDiag& p, int j, auto masked) {
+    const double dx = I.x - p.x, dy = I.y - p.y, dz = I.z - p.z;
+    double rinv = rsqrt_f64(fma(dz, dz, fma(dy, dy, fma(dx, dx, a.eps2))));
+    if (decltype(masked)::value) rinv = j > i ? rinv : 0.0;  // (lanes past the end: none)
+    const double w = p.gm * rinv, rinv2 = rinv * rinv;
+    const double xi = fma(dz, I.vz, fma(dy, I.vy, dx * I.vx));
+    const double xj = fma(dz, p.vz, fma(dy, p.vy, dx * p.vx));
+    const double q = fma(hz, p.vz, fma(hy, p.vy, hx * p.vx)) + p.q;  // q_j - 7/2 v_i.v_j
+    s0 += w;
+    s1 = fma(w, fma(-0.5 * rinv2, xi * xj, q), s1);
+    vx = fma(w, p.vx, vx);
+    vy = fma(w, p.vy, vy);
+    vz = fma(w, p.vz, vz);
+    const double c = w * rinv2 * (xi + xj);
+    yx = fma(c, dx, yx);
+    yy = fma(c, dy, yy);
+    yz = fma(c, dz, yz);
+  };
+  tri_range(
+      a, [&](int j) { pair(pk[j], j, std::true_type{}); },
+      [&](int j) {
+        const PkDiag p0 = pk[j], p1 = pk[j + 1], p2 = pk[j + 2], p3 = pk[j + 3];
+        pair(p0, j, std::false_type{});
+        pair(p1, j + 1, std::false_type{});
+        pair(p2, j + 2, std::false_type{});
+        pair(p3, j + 3, std::false_type{});
+      },
+      [&](int j) { pair(pk[j], j, std::false_type{}); });
+  double v[5] = {0, 0, 0, 0, 0};
+  if (i < a.Ns) {
+    const double m = mass[i + 1], h = -0.5 * m;
+    v[0] = -m * s0;
+    v[1] = m * fma(I.q, s0, s1);
+    v[2] = h * (fma(I.vx, s0, vx) + yx);
+    v[3] = h * (fma(I.vy, s0, vy) + yy);
+    v[4] = h * (fma(I.vz, s0, vz) + yz);
+  }
+  group_sum<5>(v, lds);
+  if (threadIdx.x < 5) row[threadIdx.x] = pick(v, threadIdx.x);
+}
+
+__global__ __launch_bounds__(kTriFinal) void k_diag_final(DiagArgs a) {
+  __shared__ double lds[14 * kTriFinal / 64];
+  double r[14];
+#pragma unroll
+  for (int c = 0; c < 14; ++c) r[c] = 0.0;
+  for (int k = threadIdx.x; k < a.nsrow; k += kTriFinal) {
+#pragma unroll
+    for (int c = 0; c < 9; ++c) r[c] += a.srow[(size_t)k * 10 + c];
+  }
+#pragma unroll 4
+  for (int k = threadIdx.x; k < a.nprow; k += kTriFinal) {
+#pragma unroll
+    for (int c = 0; c < 5; ++c) r[9 + c] += a.prow[(size_t)k * kTriRow + c];
+  }
+  group_sum<14>(r, lds);
   if (threadIdx.x == 0) {
     const double M = a.mass[0];
     const double* v1 = a.vel;
     const double v12 = v1[0] * v1[0] + v1[1] * v1[1] + v1[2] * v1[2];
     const double U0 = r[2];
-    a.out8[0] = 0.5 * M * v12 + r[0];
-    a.out8[1] = a.lam * (r[1] + 0.5 * M * U0 * U0);
+    a.out[0] = 0.5 * M * v12 + (r[0] + r[9]);
+    a.out[1] = a.lam * ((r[1] + r[10]) + 0.5 * M * U0 * U0);
     for (int c = 0; c < 3; ++c) {
-      a.out8[2 + c] = M * v1[c] + r[3 + c];
-      a.out8[5 + c] = a.lam * r[6 + c];
+      a.out[2 + c] = M * v1[c] + r[3 + c];
+      a.out[5 + c] = a.lam * (r[6 + c] + r[11 + c]);
     }
+    a.out[8] = !(M > 0.0) || !isfinite(M) ? 2.0 : 0.0;
   }
 }
 
@@ -1745,18 +1797,17 @@ __global__ __launch_bounds__(kBlock) void k_diag_final(DiagEpiArgs a) {
 struct EncArgs {
   const double* pos;
   const double* vel;
-  const PkF64* pk;  // star packets (positions)
-  int Ns, jchunk;
-  double r_close2;  // squared radius for the count
   const double* mass;
+  int Ns;
+  double r_close2;  // squared radius for the count
   double G, lam;    // gravitational constant, 1/c^2
-  double* part;     // [gridDim.y][2][Ns]: per-star nearest r^2 and partner (as double)
-  int nsplit;
-  double* bpart;    // [blocks][6]: nearest BH r^2, its star, close count, nearest pair r^2,
-                    //              largest 1PN/Newton ratio of a BH pair, its star
-  long long* bpair; // [blocks][2]: nearest pair (i, j)
-  int nb;
-  double* out;      // [8] final
+  double4* pk;      // star positions
+  double* srow;     // [star blocks][10]: nearest BH r^2, its star, close count,
+                    //                   largest 1PN/Newton ratio of a BH pair, its star
+  int nsrow;
+  double* prow;     // pair rows (TriArgs::rows): nearest pair r^2, i, j
+  int nprow;
+  double* out;      // [8]
 };
 
 // Strength of the 1PN term of a star's pair with the massive object: the
@@ -1775,141 +1826,145 @@ __device__ __forceinline__ double bh_pair_ratio(double dx, double dy, double dz,
   return lam * sqrt(tx * tx + ty * ty + tz * tz);
 }
 
-__device__ __forceinline__ bool enc_less(double r2a, long long ia, double r2b, long long ib) {
-  return r2a < r2b || (r2a == r2b && ia < ib);
+// A candidate: value and one or two indices; kNone: no star.
+constexpr int kNone = INT_MAX;
+struct EncBest {
+  double v;
+  int i, j;
+};
+// smaller value, then smaller indices (a NaN never wins)
+__device__ __forceinline__ bool enc_less(const EncBest& a, const EncBest& b) {
+  return a.v < b.v || (a.v == b.v && (a.i < b.i || (a.i == b.i && a.j < b.j)));
 }
-
-__global__ __launch_bounds__(kBlock) void k_enc_pair(EncArgs a) {
-  const PkF64* __restrict__ pk = a.pk;
-  const int i = blockIdx.x * kBlock + threadIdx.x;
-  const PkF64& pi = pk[min(i, a.Ns - 1)];
-  const double xi = pi.x, yi = pi.y, zi = pi.z;
-  const int j0 = blockIdx.y * a.jchunk, j1 = min(a.Ns, j0 + a.jchunk);
-  double best = INFINITY;
-  int bj = -1;
-  for (int j = j0; j < j1; ++j) {
-    const PkF64& p = pk[j];
-    const double dx = xi - p.x, dy = yi - p.y, dz = zi - p.z;
-    const double r2 = fma(dz, dz, fma(dy, dy, dx * dx));
-    if (j != i && r2 < best) {  // strict: the first (smallest) j wins ties
-      best = r2;
-      bj = j;
-    }
-  }
-  if (i < a.Ns) {
-    double* out = a.part + (size_t)blockIdx.y * 2 * a.Ns + i;
-    out[0] = best;
-    out[a.Ns] = (double)bj;
-  }
+__device__ __forceinline__ EncBest enc_min(const EncBest& a, const EncBest& b) {
+  return enc_less(b, a) || a.v != a.v ? b : a;
 }
-
-__global__ __launch_bounds__(kBlock) void k_enc_star(EncArgs a) {
-  __shared__ double s_r2[kBlock], s_pr2[kBlock], s_cnt[kBlock], s_z[kBlock];
-  __shared__ long long s_i[kBlock], s_pi[kBlock], s_pj[kBlock], s_zi[kBlock];
-  const int k = blockIdx.x * kBlock + threadIdx.x;
-  double r2 = INFINITY, pr2 = INFINITY, cnt = 0.0, z = -1.0;
-  long long idx = LLONG_MAX, pi_ = LLONG_MAX, pj_ = LLONG_MAX, zi = LLONG_MAX;
-  if (k < a.Ns) {
-    const double dx = a.pos[3 * (k + 1)] - a.pos[0], dy = a.pos[3 * (k + 1) + 1] - a.pos[1],
-                 dz = a.pos[3 * (k + 1) + 2] - a.pos[2];
-    r2 = dx * dx + dy * dy + dz * dz;
-    idx = k + 1;
-    cnt = r2 < a.r_close2 ? 1.0 : 0.0;
-    z = bh_pair_ratio(dx, dy, dz, r2, a.vel[3 * (k + 1)], a.vel[3 * (k + 1) + 1],
-                      a.vel[3 * (k + 1) + 2], a.G * a.mass[0], a.lam);
-    zi = k + 1;
-    for (int sp = 0; sp < a.nsplit; ++sp) {
-      const double* p = a.part + (size_t)sp * 2 * a.Ns + k;
-      const long long j = (long long)p[a.Ns];
-      if (j >= 0 && enc_less(p[0], j, pr2, pj_)) {
-        pr2 = p[0];
-        pj_ = j;
-      }
-    }
-    if (pj_ != LLONG_MAX) {  // the pair as (smaller, larger) body index
-      const long long bi = k + 1, bj = pj_ + 1;
-      pi_ = bi < bj ? bi : bj;
-      pj_ = bi < bj ? bj : bi;
-    }
+// The best over the lanes of a wavefront, in every lane.
+__device__ __forceinline__ EncBest enc_wave(EncBest b) {
+#pragma unroll
+  for (int m = 1; m < 64; m <<= 1) {
+    const EncBest o = {__shfl_xor(b.v, m, 64), __shfl_xor(b.i, m, 64), __shfl_xor(b.j, m, 64)};
+    b = enc_min(b, o);
   }
-  s_r2[threadIdx.x] = r2;
-  s_i[threadIdx.x] = idx;
-  s_cnt[threadIdx.x] = cnt;
-  s_pr2[threadIdx.x] = pr2;
-  s_pi[threadIdx.x] = pi_;
-  s_pj[threadIdx.x] = pj_;
-  s_z[threadIdx.x] = z;
-  s_zi[threadIdx.x] = zi;
+  return b;
+}
+// The best over a workgroup (its first wavefront's lanes hold it).
+__device__ __forceinline__ EncBest enc_block(EncBest b, EncBest* lds) {
+  b = enc_wave(b);
+  if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = b;
   __syncthreads();
-  for (int s = kBlock / 2; s > 0; s >>= 1) {
-    const int t = threadIdx.x;
-    if (t < s) {
-      if (enc_less(s_r2[t + s], s_i[t + s], s_r2[t], s_i[t])) {
-        s_r2[t] = s_r2[t + s];
-        s_i[t] = s_i[t + s];
-      }
-      s_cnt[t] += s_cnt[t + s];
-      const bool take = s_pr2[t + s] < s_pr2[t] ||
-                        (s_pr2[t + s] == s_pr2[t] &&
-                         (s_pi[t + s] < s_pi[t] || (s_pi[t + s] == s_pi[t] && s_pj[t + s] < s_pj[t])));
-      if (take) {
-        s_pr2[t] = s_pr2[t + s];
-        s_pi[t] = s_pi[t + s];
-        s_pj[t] = s_pj[t + s];
-      }
-      // largest ratio, ties to the smaller index (NaN ratios never win)
-      if (s_z[t + s] > s_z[t] || (s_z[t + s] == s_z[t] && s_zi[t + s] < s_zi[t])) {
-        s_z[t] = s_z[t + s];
-        s_zi[t] = s_zi[t + s];
-      }
-    }
-    __syncthreads();
+  b = lds[0];
+  for (int w = 1; w < (int)(blockDim.x >> 6); ++w) b = enc_min(b, lds[w]);
+  return b;
+}
+
+__global__ __launch_bounds__(kBlock) void k_enc_stars(EncArgs a) {
+  __shared__ EncBest lr[4], lz[4];
+  __shared__ double lc[kBlock / 64];
+  const int k = blockIdx.x * kBlock + threadIdx.x;
+  EncBest r = {INFINITY, kNone, 0}, z = {INFINITY, kNone, 0};  // z: minus the ratio
+  double cnt[1] = {0.0};
+  if (k < a.Ns) {
+    const double* x = a.pos + 3 * (size_t)(k + 1);
+    const double* v = a.vel + 3 * (size_t)(k + 1);
+    const double dx = x[0] - a.pos[0], dy = x[1] - a.pos[1], dz = x[2] - a.pos[2];
+    const double r2 = dx * dx + dy * dy + dz * dz;
+    a.pk[k] = make_double4(x[0], x[1], x[2], 0.0);
+    r = {r2, k + 1, 0};
+    z = {-bh_pair_ratio(dx, dy, dz, r2, v[0], v[1], v[2], a.G * a.mass[0], a.lam), k + 1, 0};
+    cnt[0] = r2 < a.r_close2 ? 1.0 : 0.0;
   }
+  r = enc_block(r, lr);
+  z = enc_block(z, lz);
+  group_sum<1>(cnt, lc);
   if (threadIdx.x == 0) {
-    double* b = a.bpart + 6 * (size_t)blockIdx.x;
-    b[0] = s_r2[0];
-    b[1] = (double)s_i[0];
-    b[2] = s_cnt[0];
-    b[3] = s_pr2[0];
-    b[4] = s_z[0];
-    b[5] = (double)s_zi[0];
-    a.bpair[2 * (size_t)blockIdx.x] = s_pi[0];
-    a.bpair[2 * (size_t)blockIdx.x + 1] = s_pj[0];
+    double* o = a.srow + (size_t)blockIdx.x * 10;
+    o[0] = r.v;
+    o[1] = r.i;
+    o[2] = cnt[0];
+    o[3] = z.v;
+    o[4] = z.i;
   }
 }
 
-__global__ void k_enc_final(EncArgs a) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  double r2 = INFINITY, cnt = 0.0, pr2 = INFINITY, z = -1.0;
-  long long idx = LLONG_MAX, pi_ = LLONG_MAX, pj_ = LLONG_MAX, zi = LLONG_MAX;
-  for (int b = 0; b < a.nb; ++b) {
-    const double* p = a.bpart + 6 * (size_t)b;
-    const long long bz = (long long)p[5];
-    if (p[4] > z || (p[4] == z && bz < zi)) {
-      z = p[4];
-      zi = bz;
-    }
-    const long long bi = (long long)p[1];
-    if (enc_less(p[0], bi, r2, idx)) {
-      r2 = p[0];
-      idx = bi;
-    }
-    cnt += p[2];
-    const long long qi = a.bpair[2 * (size_t)b], qj = a.bpair[2 * (size_t)b + 1];
-    if (p[3] < pr2 || (p[3] == pr2 && (qi < pi_ || (qi == pi_ && qj < pj_)))) {
-      pr2 = p[3];
-      pi_ = qi;
-      pj_ = qj;
-    }
+__global__ __launch_bounds__(kBlock) void k_enc_pair(TriArgs a,
+                                                    const double4* __restrict__ pk) {
+  __shared__ EncBest lds[4];
+  double* row = a.rows + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * kTriRow;
+  if (!tri_live(blockIdx.x, blockIdx.y, a.jchunk)) {
+    if (threadIdx.x < 3) row[threadIdx.x] = threadIdx.x == 0 ? (double)INFINITY : (double)kNone;
+    return;
   }
-  a.out[0] = sqrt(r2);
-  a.out[1] = (double)idx;
-  a.out[2] = cnt;
-  a.out[3] = sqrt(pr2);
-  a.out[4] = (double)pi_;
-  a.out[5] = (double)pj_;
-  a.out[6] = z;
-  a.out[7] = (double)zi;
+  const int i = blockIdx.x * kBlock + threadIdx.x;
+  const double4 I = pk[min(i, a.Ns - 1)];
+  auto dist2 = [&](const double4& p) {
+    const double dx = I.x - p.x, dy = I.y - p.y, dz = I.z - p.z;
+    return fma(dz, dz, fma(dy, dy, dx * dx));
+  };
+  double best = INFINITY;
+  int bj = -1;         // the first (smallest) j with the smallest r^2 ...
+  bool four_j = false; // ... or the first of the four that hold it
+  auto take = [&](double r2, int j, bool ok, bool four) {
+    const bool less = r2 < best && ok;
+    best = less ? r2 : best;
+    bj = less ? j : bj;
+    four_j = less ? four : four_j;
+  };
+  tri_range(
+      a, [&](int j) { take(dist2(pk[j]), j, j > i, false); },
+      [&](int j) {
+        const double4 p0 = pk[j], p1 = pk[j + 1], p2 = pk[j + 2], p3 = pk[j + 3];
+        // (fmin passes over a NaN, as the comparison does)
+        take(fmin(fmin(dist2(p0), dist2(p1)), fmin(dist2(p2), dist2(p3))), j, true, true);
+      },
+      [&](int j) { take(dist2(pk[j]), j, true, false); });
+  if (four_j) {
+    const int j = bj;
+    bj = dist2(pk[j]) == best ? j : dist2(pk[j + 1]) == best ? j + 1
+                                : dist2(pk[j + 2]) == best   ? j + 2
+                                                             : j + 3;
+  }
+  EncBest b = {best, bj < 0 ? kNone : i + 1, bj < 0 ? kNone : bj + 1};  // body indices, i < j
+  if (i >= a.Ns) b = {INFINITY, kNone, kNone};
+  b = enc_block(b, lds);
+  if (threadIdx.x == 0) {
+    row[0] = b.v;
+    row[1] = b.i;
+    row[2] = b.j;
+  }
+}
+
+__global__ __launch_bounds__(kTriFinal) void k_enc_final(EncArgs a) {
+  __shared__ EncBest lr[kTriFinal / 64], lz[kTriFinal / 64], lp[kTriFinal / 64];
+  __shared__ double lc[kTriFinal / 64];
+  EncBest r = {INFINITY, kNone, 0}, z = {INFINITY, kNone, 0}, p = {INFINITY, kNone, kNone};
+  double cnt[1] = {0.0};
+  for (int k = threadIdx.x; k < a.nsrow; k += kTriFinal) {
+    const double* o = a.srow + (size_t)k * 10;
+    r = enc_min(r, EncBest{o[0], (int)o[1], 0});
+    z = enc_min(z, EncBest{o[3], (int)o[4], 0});
+    cnt[0] += o[2];
+  }
+#pragma unroll 4
+  for (int k = threadIdx.x; k < a.nprow; k += kTriFinal) {
+    const double* o = a.prow + (size_t)k * kTriRow;
+    p = enc_min(p, EncBest{o[0], (int)o[1], (int)o[2]});
+  }
+  r = enc_block(r, lr);
+  z = enc_block(z, lz);
+  p = enc_block(p, lp);
+  group_sum<1>(cnt, lc);
+  if (threadIdx.x == 0) {
+    const double none = (double)LLONG_MAX;
+    a.out[0] = sqrt(r.v);
+    a.out[1] = r.i == kNone ? none : (double)r.i;
+    a.out[2] = cnt[0];
+    a.out[3] = sqrt(p.v);
+    a.out[4] = p.i == kNone ? none : (double)p.i;
+    a.out[5] = p.j == kNone ? none : (double)p.j;
+    a.out[6] = z.i == kNone ? -1.0 : -z.v;
+    a.out[7] = z.i == kNone ? none : (double)z.i;
+  }
 }
 
 // ---------------------------------------------------------------------------
