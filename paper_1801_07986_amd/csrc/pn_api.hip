@@ -48,7 +48,20 @@ struct Shape {
   int nsplit = 1;  // j splits (gridDim.y)
   int jchunk = 1;  // j per split
   int iblocks = 1; // gridDim.x
+  int dsplit = 1;  // j splits of the jerk sweep
+  int djchunk = 1; // j per split there
 };
+// j splits of the jerk sweep (64 i-bodies and 4 wavefronts per workgroup, at
+// most 4 workgroups resident per CU): 24, which is fastest or within 1 % of it
+// from N = 1024 to 16384 (N = 2048: 60.9 us per Hermite step, 69.7 with 12;
+// 8192: 405 and 418; 16384: 1452 and 1467), fewer where a wavefront would get
+// less than 8 j (N = 300: 31.6 with 8 or 9, 33.9 with 24), and no more than
+// give 6144 workgroups where there are many i-bodies (the partial sums grow
+// with the splits), 8 at least.
+int dual_splits(int Ns) {
+  const int iblocks = (Ns + 63) / 64;
+  return std::max(1, std::min({24, Ns / 32, std::max(8, 6144 / iblocks)}));
+}
 
 // Tuned shapes installed with pn_set_shape (searched by the autotuner).
 struct TunedShape {
@@ -95,6 +108,9 @@ Shape pick_shape(int Ns, int precision) {
   want_nsplit = std::max(1, std::min(want_nsplit, Ns));
   s.jchunk = (Ns + want_nsplit - 1) / want_nsplit;
   s.nsplit = (Ns + s.jchunk - 1) / s.jchunk;
+  const int ds = dual_splits(Ns);
+  s.djchunk = (Ns + ds - 1) / ds;
+  s.dsplit = (Ns + s.djchunk - 1) / s.djchunk;
   return s;
 }
 
@@ -172,7 +188,7 @@ Layout layout_for(int64_t N, const Shape& s, Need need, int stage_ns = 0) {
   L.bpart = take(nrows * 8 * W * sizeof(double));
   L.ub2 = take(rk4 || dual ? Ns * 4 * W * sizeof(double) : 0);
   L.bpart2 = take(rk4 || dual ? nrows * 8 * W * sizeof(double) : 0);
-  L.part = take((size_t)s.nsplit * kNF * W * Ns * sizeof(double));
+  L.part = take((size_t)std::max(s.nsplit, dual ? 2 * s.dsplit : 0) * kNF * Ns * sizeof(double));
   L.bhpart = take(nepi * 4 * W * sizeof(double));
   L.bhpart2 = take(dual || fused ? nepi * 4 * W * sizeof(double) : 0);
   L.pk2 = take(fused ? Ns * sizeof(PkF64) : 0);
@@ -463,16 +479,16 @@ int launch_pair(const Sys& s, const Ptrs& P, const Shape& sh, int precision, int
 }
 
 // The jerk sweep: FP64 dual numbers, one i per lane, four wavefronts per
-// i-range, the j-splits of the evaluation's shape.
+// i-range, dual_splits j-splits.
 int launch_pair_dual(const Sys& s, const Ptrs& P, const Shape& sh, hipStream_t st) {
   PairArgs a;
   a.pk = P.at<void>(P.L.pk);
   a.Ns = (int)(s.N - 1);
-  a.jchunk = sh.jchunk;
+  a.jchunk = sh.djchunk;
   a.eps2 = s.eps * s.eps;
   a.part = P.at<double>(P.L.part);
   const int iblocks = (a.Ns + 63) / 64;
-  hipLaunchKernelGGL((k_pair<Dual, MODE_FUSED, 1, 4>), dim3(iblocks, sh.nsplit), dim3(kBlock), 0,
+  hipLaunchKernelGGL((k_pair<Dual, MODE_FUSED, 1, 4>), dim3(iblocks, sh.dsplit), dim3(kBlock), 0,
                      st, a);
   HIPCK(hipGetLastError());
   return PN_OK;
@@ -525,7 +541,7 @@ EpiArgs epi_args(const Sys& s, const Ptrs& P, const Shape& sh, const Outs& o) {
   a.bpart = P.at<double>(P.L.bpart);
   a.nbpro = ne;
   a.part = P.at<double>(P.L.part);
-  a.nsplit = sh.nsplit;
+  a.nsplit = o.dual ? sh.dsplit : sh.nsplit;
   a.newton_only = o.newton_only ? 1 : 0;
   a.phi_in = o.phi_in;
   a.accN_in = o.accN_in;
