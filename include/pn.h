@@ -30,9 +30,9 @@
  *   internal scratch, kept per device and grown on demand, and (pn_step) cached
  *   HIP graphs; pn_release() frees both.  No argument pointer is kept after the
  *   call returns, except inside the cached step graphs of pn_step,
- *   pn_step_hermite (one step, and 16 steps per replay for long runs) and
- *   pn_step_batched, which are re-captured when any pointer or parameter
- *   changes.
+ *   pn_step_hermite (16 steps per replay) and pn_step_batched.  A graph is
+ *   captured once 256 steps in a row were asked for with the same pointers and
+ *   parameters, and used for those only; other steps are launched directly.
  * - Return codes: PN_OK, or one of the negative codes below.  No C++ exception
  *   crosses the ABI.  Outputs are unspecified after an error, except
  *   PN_ENONFINITE, where all outputs are written.
@@ -69,7 +69,7 @@ extern "C" {
 
 /* flags */
 #define PN_ASYNC 1   /* see above */
-#define PN_NOGRAPH 2 /* pn_step: launch kernels directly instead of replaying a graph */
+#define PN_NOGRAPH 2 /* pn_step: launch every step directly, never replay a graph */
 #define PN_TIMING 4  /* pn_step / pn_accel: time every pair-kernel launch with HIP events
                         (implies PN_NOGRAPH); read with pn_last_timing() */
 

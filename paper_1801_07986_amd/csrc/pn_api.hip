@@ -288,11 +288,11 @@ struct DevState {
   char* base = nullptr;
   size_t cap = 0;
   char* fixed = nullptr;  // this device's copy of `scratch` (pn_accel_noalloc)
-  hipGraph_t graph = nullptr;      // one time step
+  hipGraph_t graph = nullptr;      // kStepsPerGraph time steps
   hipGraphExec_t gexec = nullptr;
-  hipGraph_t graph_k = nullptr;    // kStepsPerGraph time steps
-  hipGraphExec_t gexec_k = nullptr;
-  GraphKey key;  // the system both graphs were captured for
+  GraphKey key;    // the system the graph was captured for
+  GraphKey asked;  // the system of the last stepping call ...
+  int64_t asked_steps = 0;  // ... and its steps in a row
   std::vector<hipEvent_t> ev;
   // batched ensembles: own scratch and step graph
   char* bbase = nullptr;
@@ -302,6 +302,7 @@ struct DevState {
   BatchKey bkey;   // ensemble the cached graph was captured for
   BatchKey bdesc;  // ensemble whose descriptors are in the batched scratch now
   bool bdesc_valid = false;
+  int64_t basked_steps = 0;  // steps in a row of the ensemble in bdesc
   // every call's device work shares the scratch above: a call on another
   // stream than the previous one waits for it (last_ev recorded on last_st)
   hipEvent_t last_ev = nullptr;
@@ -330,12 +331,8 @@ int dev_state(DevState** out) {
 void drop_graph(DevState& d) {
   if (d.gexec) (void)hipGraphExecDestroy(d.gexec);
   if (d.graph) (void)hipGraphDestroy(d.graph);
-  if (d.gexec_k) (void)hipGraphExecDestroy(d.gexec_k);
-  if (d.graph_k) (void)hipGraphDestroy(d.graph_k);
   d.gexec = nullptr;
   d.graph = nullptr;
-  d.gexec_k = nullptr;
-  d.graph_k = nullptr;
   d.key = GraphKey();
 }
 
@@ -992,11 +989,19 @@ hipStream_t pick_stream(DevState& d, void* stream) {
 }
 
 
-// Time steps per replay of the long graph.  Consecutive graph launches are
-// separated by several microseconds more than kernels within one graph (at
-// N = 1024 about 6.5 against 1.1-1.7 us, against a step of about 60 us), so
-// long runs replay kStepsPerGraph steps per launch.
+// Time steps per replay of the step graph.  Consecutive graph launches are
+// separated by several microseconds more than kernels within one graph, so a
+// graph holds kStepsPerGraph steps; steps left over are launched directly.
 constexpr int kStepsPerGraph = 16;
+
+// The graph is captured once this many steps have been asked for in a row with
+// one set of buffers and parameters (in one call or several); until then, and
+// for steps left over, the kernels are launched directly.  Capturing takes
+// 230-350 us (N = 1024: 32 steps on new buffers 1856 us launched directly, 2099
+// with the capture; N = 3000, mixed, 8 steps: 774 and 1033), and replaying saves
+// at most 1.4 us a step (N = 1024: 52.0 against 53.4 us; N = 100: 36.1 and 36.3;
+// nothing from N = 10001 on, where the launches hide behind the sweeps).
+constexpr int64_t kGraphAfterSteps = 256;
 
 // Captures `steps` time steps (on the library's own stream) into *graph/*exec.
 template <typename Enqueue>
@@ -1024,26 +1029,28 @@ int capture_steps(DevState& d, int steps, Enqueue& enqueue_step, hipGraph_t* gra
   return PN_OK;
 }
 
-// Replays the captured time step nsteps times on `st`: kStepsPerGraph steps
-// per launch of the long graph, the rest one per launch.  Both graphs are
-// captured on the first call for a key (a new key drops both), so that a
-// short warm-up call leaves a long run nothing to capture.  The steps and
-// their order are those of direct launches, so are the results.
+// Enqueues nsteps time steps on `st`: by replays of the captured graph where
+// one is cached for this key or worth capturing, the rest directly.  The steps
+// and their order are the same, so are the results.
 template <typename Enqueue>
-int replay_step(DevState& d, const GraphKey& key, int64_t nsteps, hipStream_t st,
-                Enqueue enqueue_step) {
-  if (!(key == d.key)) drop_graph(d);
-  const int64_t nlong = nsteps / kStepsPerGraph, nshort = nsteps % kStepsPerGraph;
+int run_steps(DevState& d, const GraphKey& key, int64_t nsteps, hipStream_t st,
+              Enqueue enqueue_step) {
   int rc;
-  if (!d.gexec_k) {
-    if ((rc = capture_steps(d, kStepsPerGraph, enqueue_step, &d.graph_k, &d.gexec_k))) return rc;
+  if (!(key == d.asked)) {
+    d.asked = key;
+    d.asked_steps = 0;
   }
-  if (!d.gexec) {
-    if ((rc = capture_steps(d, 1, enqueue_step, &d.graph, &d.gexec))) return rc;
+  d.asked_steps += nsteps;
+  if (d.asked_steps >= kGraphAfterSteps && !(key == d.key)) {
+    drop_graph(d);
+    if ((rc = capture_steps(d, kStepsPerGraph, enqueue_step, &d.graph, &d.gexec))) return rc;
+    d.key = key;
   }
-  d.key = key;
-  for (int64_t k = 0; k < nlong; ++k) HIPCK(hipGraphLaunch(d.gexec_k, st));
-  for (int64_t k = 0; k < nshort; ++k) HIPCK(hipGraphLaunch(d.gexec, st));
+  int64_t k = 0;
+  if (key == d.key)
+    for (; k + kStepsPerGraph <= nsteps; k += kStepsPerGraph) HIPCK(hipGraphLaunch(d.gexec, st));
+  for (; k < nsteps; ++k)
+    if ((rc = enqueue_step(st))) return rc;
   return PN_OK;
 }
 
@@ -1426,7 +1433,7 @@ int pn_step(double* pos, double* vel, const double* mass, int64_t N, double G, d
   const bool graph = !(flags & (PN_NOGRAPH | PN_TIMING));
   if (nsteps > 0 && ns > 0) {
     // one launch per stage: the head, the first step, nsteps - 1 further
-    // steps (replayed from a graph), the last pending update
+    // steps (run_steps), the last pending update
     Timer tm;
     tm.d = d;
     tm.on = timing;
@@ -1450,7 +1457,7 @@ int pn_step(double* pos, double* vel, const double* mass, int64_t N, double G, d
         key.precision = precision;
         key.stage_ns = ns;
         key.base = d->base;
-        rc = replay_step(*d, key, nsteps - 1, st, [&](hipStream_t cs) {
+        rc = run_steps(*d, key, nsteps - 1, st, [&](hipStream_t cs) {
           return enqueue_stage_step(s, P, sh, precision, dt, pos, vel, ns, false, cs, nullptr);
         });
         if (rc) return rc;
@@ -1484,11 +1491,11 @@ int pn_step(double* pos, double* vel, const double* mass, int64_t N, double G, d
       key.ws = sh.ws;
       key.nsplit = sh.nsplit;
       key.base = d->base;
-      // the first sweep, nsteps - 1 replayed steps (each ending in the next
-      // step's first sweep), and the last step launched directly
+      // the first sweep, nsteps - 1 steps (each ending in the next step's first
+      // sweep), and the last step
       if ((rc = enqueue_rk4_head(s, P, sh, precision, dt, pos, vel, st, nullptr))) return rc;
       if (nsteps > 1) {
-        rc = replay_step(*d, key, nsteps - 1, st, [&](hipStream_t cs) {
+        rc = run_steps(*d, key, nsteps - 1, st, [&](hipStream_t cs) {
           return enqueue_rk4_body(s, P, sh, precision, dt, pos, vel, true, cs, nullptr);
         });
         if (rc) return rc;
@@ -1559,7 +1566,7 @@ int pn_step_hermite(double* pos, double* vel, const double* mass, int64_t N, dou
       key.ws = sh.ws;
       key.nsplit = sh.nsplit;
       key.base = d->base;
-      rc = replay_step(*d, key, nsteps, st, [&](hipStream_t cs) {
+      rc = run_steps(*d, key, nsteps, st, [&](hipStream_t cs) {
         return enqueue_hermite_step(s, P, sh, dt, pos, vel, cs);
       });
       if (rc) return rc;
@@ -1715,31 +1722,33 @@ int pn_step_batched(int32_t n_sys, const int64_t* offsets, const double* G, cons
     HIPCK(hipStreamSynchronize(st));
     d->bdesc = key;
     d->bdesc_valid = true;
+    d->basked_steps = 0;
   }
   hipLaunchKernelGGL(k_reset_status, dim3(1), dim3(64), 0, st, status);
   HIPCK(hipGetLastError());
   if (nsteps > 0) {
-    if (!graph) {
-      for (int64_t k = 0; k < nsteps; ++k)
-        if ((rc = enqueue_batched_step(P, base, mass, pos, vel, dt, precision, st))) return rc;
-    } else {
-      if (!(d->bgexec && key == d->bkey)) {
-        drop_batch_graph(*d);
-        HIPCK(hipStreamSynchronize(d->own));
-        HIPCK(hipStreamBeginCapture(d->own, hipStreamCaptureModeThreadLocal));
-        rc = enqueue_batched_step(P, base, mass, pos, vel, dt, precision, d->own);
-        hipGraph_t g = nullptr;
-        hipError_t e = hipStreamEndCapture(d->own, &g);
-        if (rc) {
-          if (g) (void)hipGraphDestroy(g);
-          return rc;
-        }
-        if (e != hipSuccess) return fail_hip(e, "hipStreamEndCapture", __LINE__);
-        d->bgraph = g;
-        HIPCK(hipGraphInstantiate(&d->bgexec, d->bgraph, nullptr, nullptr, 0));
-        d->bkey = key;
+    const bool cached = d->bgexec && key == d->bkey;
+    d->basked_steps += nsteps;
+    if (graph && !cached && d->basked_steps >= kGraphAfterSteps) {
+      drop_batch_graph(*d);
+      HIPCK(hipStreamSynchronize(d->own));
+      HIPCK(hipStreamBeginCapture(d->own, hipStreamCaptureModeThreadLocal));
+      rc = enqueue_batched_step(P, base, mass, pos, vel, dt, precision, d->own);
+      hipGraph_t g = nullptr;
+      hipError_t e = hipStreamEndCapture(d->own, &g);
+      if (rc) {
+        if (g) (void)hipGraphDestroy(g);
+        return rc;
       }
-      for (int64_t k = 0; k < nsteps; ++k) HIPCK(hipGraphLaunch(d->bgexec, st));
+      if (e != hipSuccess) return fail_hip(e, "hipStreamEndCapture", __LINE__);
+      d->bgraph = g;
+      HIPCK(hipGraphInstantiate(&d->bgexec, d->bgraph, nullptr, nullptr, 0));
+      d->bkey = key;
+    }
+    const bool replay = graph && d->bgexec && key == d->bkey;
+    for (int64_t k = 0; k < nsteps; ++k) {
+      if (replay) HIPCK(hipGraphLaunch(d->bgexec, st));
+      else if ((rc = enqueue_batched_step(P, base, mass, pos, vel, dt, precision, st))) return rc;
     }
   }
   if ((rc = mark_call_end(*d, st))) return rc;
