@@ -261,12 +261,38 @@ __device__ __forceinline__ double dpp_d(double x) {
   return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
 }
 
+// x plus the x of lane i ^ 16 (i ^ 32), by one row swap of each 32-bit half:
+// v_permlane16_swap exchanges the odd rows of 16 of its first operand with the
+// even rows of its second, so on two copies of x the first ends with the even
+// row of each pair of rows in both, the second with the odd one
+// (v_permlane32_swap: the same with halves of 32).  Both lanes add the same two
+// values.
+template <int M>
+__device__ __forceinline__ double swap_sum(double x) {
+  static_assert(M == 16 || M == 32, "row or half");
+  const unsigned long long u = __builtin_bit_cast(unsigned long long, x);
+  const unsigned lo = (unsigned)u, hi = (unsigned)(u >> 32);
+  if constexpr (M == 16) {
+    const auto a = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    const auto b = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    return __builtin_bit_cast(double, ((unsigned long long)b[0] << 32) | a[0]) +
+           __builtin_bit_cast(double, ((unsigned long long)b[1] << 32) | a[1]);
+  } else {
+    const auto a = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+    const auto b = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+    return __builtin_bit_cast(double, ((unsigned long long)b[0] << 32) | a[0]) +
+           __builtin_bit_cast(double, ((unsigned long long)b[1] << 32) | a[1]);
+  }
+}
+
 // Sum over the 64 lanes of a wavefront by six exchanges: lane i with 7 - i
 // (within 8), i ^ 1, i ^ 2, 15 - i (within 16), i ^ 16, i ^ 32.  Both lanes
 // of every exchange add the same two values, so after each level the lanes it
 // joined hold the same bits, and at the end every lane holds the same sum; no
 // barrier.  The first four levels are DPP moves within a row, the last two
-// go through the LDS crossbar (ds_bpermute).
+// row swaps (swap_sum), all in the vector unit (through the LDS crossbar,
+// ds_bpermute, those two levels cost a step 2.5 % at N = 100, 35.4 against 34.6
+// us, and 1.3 % at N = 1024, 51.5 against 50.8).
 template <int K>
 __device__ __forceinline__ void wave_allsum(double (&v)[K]) {
 #pragma unroll
@@ -278,9 +304,9 @@ __device__ __forceinline__ void wave_allsum(double (&v)[K]) {
 #pragma unroll
   for (int k = 0; k < K; ++k) v[k] += dpp_d<0x140>(v[k]);
 #pragma unroll
-  for (int k = 0; k < K; ++k) v[k] += __shfl_xor(v[k], 16, 64);
+  for (int k = 0; k < K; ++k) v[k] = swap_sum<16>(v[k]);
 #pragma unroll
-  for (int k = 0; k < K; ++k) v[k] += __shfl_xor(v[k], 32, 64);
+  for (int k = 0; k < K; ++k) v[k] = swap_sum<32>(v[k]);
 }
 
 // Element col of a register array, chosen per lane without indexing the
