@@ -175,7 +175,7 @@ def tune_batched(log=print, steps=2, reps=2):
     return out
 
 
-STAGE_SIZES = [100, 300, 1024, 2048, 4096]
+STAGE_SIZES = [100, 160, 512, 1024, 2048, 4096]
 STAGE_NS = (2, 4, 8, 16)
 
 
@@ -218,7 +218,13 @@ def tune_stage(log=print):
             if r["ns"] == 0:
                 continue
             lo = 2 if k == 0 else int(math.sqrt(rs[k - 1]["N"] * r["N"])) + 1
+            if k > 0 and rs[k - 1]["ns"] > 0:
+                lo = entries[-1]["n_max"] + 1
             hi = int(math.sqrt(r["N"] * (rs[k + 1]["N"] if k + 1 < len(rs) else 2 * r["N"])))
+            # a workgroup fills a CU's wavefront slots: beyond one per CU the
+            # rest wait for a second pass (FP64, 4 stars per workgroup: N = 1025
+            # 37.1 us per step, 1100 69.4)
+            hi = max(min(hi, 256 * r["ns"] + 1), r["N"])
             entries.append(dict(precision=prec, n_min=lo, n_max=hi, ns=r["ns"], measured_N=r["N"],
                                 step_ms=round(r["step_ms"], 5),
                                 chain_step_ms=round(r["chain_step_ms"], 5)))

@@ -149,7 +149,7 @@ size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 struct Layout {
   size_t pk, ub, bpart, ub2, bpart2, bhpart2, part, bhpart, status, xs, vs, kx, kv, ha, hj, xp, vp, ap,
-      pk2, bpart3, bpart4, bhs, total;
+      pk2, bhs, total;
 };
 
 // What a call needs beyond one force evaluation: the RK4 stage arrays, or the
@@ -158,7 +158,7 @@ struct Layout {
 enum class Need { EVAL, RK4, JERK, HERMITE };
 
 // stage_ns > 0 (RK4 only): the one-launch stages' extra buffers (k_stage:
-// a second packet buffer, four block-row buffers of a row per stage_ns stars,
+// a second packet buffer, two block-row buffers of a row per stage_ns stars,
 // two massive-object row buffers and two copies of its state).
 Layout layout_for(int64_t N, const Shape& s, Need need, int stage_ns = 0) {
   const bool rk4 = need == Need::RK4;
@@ -192,9 +192,7 @@ Layout layout_for(int64_t N, const Shape& s, Need need, int stage_ns = 0) {
   L.bhpart = take(nepi * 4 * W * sizeof(double));
   L.bhpart2 = take(dual || fused ? nepi * 4 * W * sizeof(double) : 0);
   L.pk2 = take(fused ? Ns * sizeof(PkF64) : 0);
-  L.bpart3 = take(fused ? nbf * 8 * sizeof(double) : 0);
-  L.bpart4 = take(fused ? nbf * 8 * sizeof(double) : 0);
-  L.bhs = take(fused ? 36 * sizeof(double) : 0);
+  L.bhs = take(fused ? 2 * kBhState * sizeof(double) : 0);
   L.status = take(sizeof(int));
   const size_t n3 = 3 * (size_t)N * sizeof(double);
   L.xs = take(rk4 ? n3 : 0);
@@ -772,12 +770,12 @@ int enqueue_rk4_body(const Sys& s, const Ptrs& P, const Shape& sh, int precision
 }
 
 // One-launch Runge-Kutta stages (k_stage, small systems).  Buffers of stage k:
-// packets and u/b rows k % 2, block rows k % 4, massive-object 1PN rows
-// k % 2, massive-object state read from copy k % 2 and written to the other.
+// packets, u/b rows, block rows and massive-object 1PN rows k % 2 (written:
+// the other), massive-object state read from copy k % 2.
 struct StageBufs {
   void* pk[2];
   double* ub[2];
-  double* bpart[4];
+  double* bpart[2];
   double* bhpart[2];
   double* bhs[2];
   int nb;  // workgroups = rows per row buffer
@@ -790,19 +788,21 @@ StageBufs stage_bufs(const Ptrs& P, int64_t N, int ns) {
   b.ub[1] = P.at<double>(P.L.ub2);
   b.bpart[0] = P.at<double>(P.L.bpart);
   b.bpart[1] = P.at<double>(P.L.bpart2);
-  b.bpart[2] = P.at<double>(P.L.bpart3);
-  b.bpart[3] = P.at<double>(P.L.bpart4);
   b.bhpart[0] = P.at<double>(P.L.bhpart);
   b.bhpart[1] = P.at<double>(P.L.bhpart2);
   b.bhs[0] = P.at<double>(P.L.bhs);
-  b.bhs[1] = b.bhs[0] + 18;
+  b.bhs[1] = b.bhs[0] + kBhState;
   b.nb = (int)((N - 1 + ns - 1) / ns);
   return b;
 }
 
 template <typename T, int NS>
 void launch_stage_t(const StageArgs& sa, int grid, hipStream_t st) {
-  hipLaunchKernelGGL((k_stage<T, NS>), dim3(grid), dim3(kBlock), 0, st, sa);
+  // one j per lane at most: each lane loads its own packet
+  if (sa.e.Ns <= 64 * kStageWaves / NS)
+    hipLaunchKernelGGL((k_stage<T, NS, true>), dim3(grid), dim3(kStageThreads), 0, st, sa);
+  else
+    hipLaunchKernelGGL((k_stage<T, NS, false>), dim3(grid), dim3(kStageThreads), 0, st, sa);
 }
 template <typename T>
 int launch_stage_ns(const StageArgs& sa, int grid, int ns, hipStream_t st) {
@@ -827,19 +827,18 @@ int launch_stage(const Sys& s, const Ptrs& P, const Shape& sh, int precision, do
   EpiArgs a = epi_args(e, P, sh, o);
   const StageBufs b = stage_bufs(P, s.N, ns);
   a.ub = b.ub[stage & 1];
-  a.bpart = b.bpart[stage];
+  a.bpart = b.bpart[stage & 1];
   a.nbpro = b.nb;
   a.bhpart = b.bhpart[stage & 1];
   a.nbepi = b.nb;
   a.pk_next = b.pk[(stage + 1) & 1];
   a.ub_next = b.ub[(stage + 1) & 1];
-  a.bpart_next = b.bpart[(stage + 1) & 3];
+  a.bpart_next = b.bpart[(stage + 1) & 1];
   StageArgs sa;
   sa.e = a;
   sa.pk = b.pk[stage & 1];
   sa.mode = mode;
   sa.pstage = (stage + 3) & 3;
-  sa.prow = b.bpart[(stage + 3) & 3];
   sa.phrow = b.bhpart[((stage + 3) & 3) & 1];
   sa.bhs_in = b.bhs[stage & 1];
   sa.bhs_out = b.bhs[(stage + 1) & 1];
@@ -850,12 +849,12 @@ int launch_stage(const Sys& s, const Ptrs& P, const Shape& sh, int precision, do
 
 // A call's first packets and rows in the stage kernel's layout.
 template <typename T>
-int launch_stage_head_t(const EpiArgs& a, int grid, int ns, hipStream_t st) {
+int launch_stage_head_t(const EpiArgs& a, double* bhs, int grid, int ns, hipStream_t st) {
   switch (ns) {
-    case 2: hipLaunchKernelGGL((k_stage_head<T, 2>), dim3(grid), dim3(kBlock), 0, st, a); break;
-    case 4: hipLaunchKernelGGL((k_stage_head<T, 4>), dim3(grid), dim3(kBlock), 0, st, a); break;
-    case 8: hipLaunchKernelGGL((k_stage_head<T, 8>), dim3(grid), dim3(kBlock), 0, st, a); break;
-    case 16: hipLaunchKernelGGL((k_stage_head<T, 16>), dim3(grid), dim3(kBlock), 0, st, a); break;
+    case 2: hipLaunchKernelGGL((k_stage_head<T, 2>), dim3(grid), dim3(kBlock), 0, st, a, bhs); break;
+    case 4: hipLaunchKernelGGL((k_stage_head<T, 4>), dim3(grid), dim3(kBlock), 0, st, a, bhs); break;
+    case 8: hipLaunchKernelGGL((k_stage_head<T, 8>), dim3(grid), dim3(kBlock), 0, st, a, bhs); break;
+    case 16: hipLaunchKernelGGL((k_stage_head<T, 16>), dim3(grid), dim3(kBlock), 0, st, a, bhs); break;
     default: return fail_inval("stars per workgroup of the stage kernel: 2, 4, 8 or 16");
   }
   HIPCK(hipGetLastError());
@@ -869,8 +868,8 @@ int launch_stage_head(const Sys& s, const Ptrs& P, const Shape& sh, int precisio
   a.pk_next = b.pk[0];
   a.ub_next = b.ub[0];
   a.bpart_next = b.bpart[0];
-  return precision == PN_MIXED ? launch_stage_head_t<float>(a, b.nb, ns, st)
-                               : launch_stage_head_t<double>(a, b.nb, ns, st);
+  return precision == PN_MIXED ? launch_stage_head_t<float>(a, b.bhs[0], b.nb, ns, st)
+                               : launch_stage_head_t<double>(a, b.bhs[0], b.nb, ns, st);
 }
 
 // The four stages of one step; the first step of a call starts without a

@@ -309,6 +309,26 @@ __device__ __forceinline__ void wave_allsum(double (&v)[K]) {
   for (int k = 0; k < K; ++k) v[k] = swap_sum<32>(v[k]);
 }
 
+// Sums over lanes 0 .. NS - 1 of a wavefront, in each of them.
+template <int NS, int K>
+__device__ __forceinline__ void star_sum(double (&v)[K]) {
+  static_assert(NS == 2 || NS == 4 || NS == 8 || NS == 16, "stars per workgroup");
+#pragma unroll
+  for (int k = 0; k < K; ++k) v[k] += dpp_d<0xB1>(v[k]);
+  if constexpr (NS >= 4) {
+#pragma unroll
+    for (int k = 0; k < K; ++k) v[k] += dpp_d<0x4E>(v[k]);
+  }
+  if constexpr (NS >= 8) {
+#pragma unroll
+    for (int k = 0; k < K; ++k) v[k] += dpp_d<0x141>(v[k]);
+  }
+  if constexpr (NS >= 16) {
+#pragma unroll
+    for (int k = 0; k < K; ++k) v[k] += dpp_d<0x140>(v[k]);
+  }
+}
+
 // Element col of a register array, chosen per lane without indexing the
 // array at run time (a chain of selects).
 template <int K>
@@ -1033,95 +1053,287 @@ __device__ __forceinline__ bool epi_field_used(int f, const EpiArgs& a) {
 // massive object's next position; Dual, the jerk sweep's at this state, with
 // the derivatives (v, a) of (x, v) from the acceleration just computed.
 // void: none.
-// The massive object's state at an evaluation, for an epilogue whose kernel
-// computes it (the one-launch Runge-Kutta stage) instead of reading it.
-struct BhStage {
-  double x0[3];  // evaluation position
-  double X[3];   // step-start position
-  double KX[3];  // stage sum of its velocities through the previous stage
-  double v[3];   // evaluation velocity
-};
 
-// The epilogue of NSTAR stars (blk * NSTAR ...), from the prologue rows `rows`
-// (this thread's rows_load).  OWNBH = false: the stars' pair sums are the
-// nsplit partials in a.part, the massive object's state is read from a.pos,
-// a.X, a.KX, a.vel.  OWNBH = true (S = double only): the caller has put the
-// pair sums in fsum[field][NSTAR] and passes the massive object's state in own.
-template <typename S, typename PkT, int NSTAR, bool OWNBH>
-__device__ __forceinline__ void epilogue_rows(const EpiArgs& a, int blk, double* lds,
-                                              double* fsum, const double (&rows)[bh_cols<S>()],
-                                              const BhStage& own) {
-  constexpr bool DUAL = IsDual<S>::value;
-  constexpr int W = DUAL ? 2 : 1;
-  constexpr int NFO = kNF * W;
-  static_assert(NSTAR <= 64, "the stars of a workgroup are in its first wavefront");
-  static_assert(OWNBH || NSTAR == kEpiStars, "the split reduction takes 4 threads per star");
-  static_assert(!OWNBH || (!DUAL && !std::is_void<PkT>::value), "own state: chained FP64 epilogue");
-  // Every global read of the workgroup is requested before the first wait:
-  // the prologue rows (by the caller), the pair partials, the star's own
-  // inputs and Runge-Kutta state, the massive object's state.  (At small N
-  // this kernel is a chain of memory latencies; issued in order, they added
-  // up.)
-  const double M = a.mass[0];
-  S x0, y0, z0;
-  if constexpr (OWNBH) {
-    x0 = own.x0[0];
-    y0 = own.x0[1];
-    z0 = own.x0[2];
-  } else {
-    x0 = ld<S>(a.pos, a.pos_d, 0);
-    y0 = ld<S>(a.pos, a.pos_d, 1);
-    z0 = ld<S>(a.pos, a.pos_d, 2);
-  }
-  const int k = blk * NSTAR + threadIdx.x;
-  const bool star = threadIdx.x < NSTAR && k < a.Ns;
-  const int i = k + 1;
-  S ui = 0.0, bx = 0.0, by = 0.0, bz = 0.0, xi = 0.0, yi = 0.0, zi = 0.0;
-  S vi[3] = {0.0, 0.0, 0.0};
+// A star's own inputs, read ahead of their use.
+template <typename S>
+struct EpiStar {
+  S u = 0.0, bx = 0.0, by = 0.0, bz = 0.0, x = 0.0, y = 0.0, z = 0.0;
+  S v[3] = {0.0, 0.0, 0.0};
   double m_s = 0.0;  // the star's mass (G m is formed where it is used, after the loads)
   Rk4In rk[3];
-  // the massive object's step-start position, stage sum and velocity (uniform:
-  // scalar loads)
-  double bh_x[3] = {0.0, 0.0, 0.0}, bh_kx[3] = {0.0, 0.0, 0.0}, bh_v[3] = {0.0, 0.0, 0.0};
-  if constexpr (OWNBH) {
-    for (int c = 0; c < 3; ++c) {
-      bh_x[c] = own.X[c];
-      bh_kx[c] = a.stage == 0 ? 0.0 : own.KX[c];
-      bh_v[c] = own.v[c];
+};
+template <typename S>
+__device__ __forceinline__ EpiStar<S> epi_star_load(const EpiArgs& a, int k) {
+  constexpr int W = Width<S>::n;
+  const int i = k + 1;
+  EpiStar<S> in;
+  const double* ub = a.ub + 4 * W * (size_t)k;
+  in.u = get<S>(ub, 0, 4);
+  in.bx = get<S>(ub, 1, 4);
+  in.by = get<S>(ub, 2, 4);
+  in.bz = get<S>(ub, 3, 4);
+  in.x = ld<S>(a.pos, a.pos_d, 3 * i);
+  in.y = ld<S>(a.pos, a.pos_d, 3 * i + 1);
+  in.z = ld<S>(a.pos, a.pos_d, 3 * i + 2);
+  if (!a.newton_only) {
+    in.v[0] = ld<S>(a.vel, a.vel_d, 3 * i);
+    in.v[1] = ld<S>(a.vel, a.vel_d, 3 * i + 1);
+    in.v[2] = ld<S>(a.vel, a.vel_d, 3 * i + 2);
+    in.m_s = a.mass[i];
+  }
+  if constexpr (!IsDual<S>::value) {
+    for (int c = 0; c < 3; ++c) in.rk[c] = rk4_load(a, 3 * (size_t)i + c);
+  }
+  return in;
+}
+
+// The massive object at an evaluation: its mass, its position, its acceleration A0 and
+// potential magnitude V0, w = -P / M; and, for a chained Runge-Kutta stage, its
+// step-start position, the stage sum of its velocities through the previous
+// stage and its velocity.
+template <typename S>
+struct EpiBh {
+  double M;
+  S x0[3], A0[3], V0, w[3];
+  double X[3] = {0.0, 0.0, 0.0}, KX[3] = {0.0, 0.0, 0.0}, v[3] = {0.0, 0.0, 0.0};
+};
+
+template <typename PkT>
+constexpr int epi_next_terms() {  // block-sum terms of the next prologue
+  return std::is_same<PkT, Dual>::value ? 14 : 7;
+}
+
+// What the epilogue of a star needs of it and the massive object that does not
+// wait for its pair sums.
+template <typename S>
+struct EpiGeo {
+  S vi2, d0[3], rinv0, n0[3], kk, vw, dA, n4v, nw, g7;  // the star's own terms
+  S ks, nvs, nws, g7s;                                  // the massive object's
+};
+template <typename S>
+__device__ __forceinline__ EpiGeo<S> epi_geo(const EpiArgs& a, const EpiStar<S>& in,
+                                             const EpiBh<S>& B) {
+  EpiGeo<S> g;
+  const double gM = a.G * B.M;
+  const S (&vi)[3] = in.v;
+  g.vi2 = vi[0] * vi[0] + vi[1] * vi[1] + vi[2] * vi[2];
+  g.d0[0] = in.x - B.x0[0];
+  g.d0[1] = in.y - B.x0[1];
+  g.d0[2] = in.z - B.x0[2];
+  g.rinv0 = rsqrt_t(g.d0[0] * g.d0[0] + g.d0[1] * g.d0[1] + g.d0[2] * g.d0[2] + a.eps2);
+  for (int c = 0; c < 3; ++c) g.n0[c] = g.d0[c] * g.rinv0;
+  g.kk = gM * g.rinv0 * g.rinv0;
+  g.vw = vi[0] * B.w[0] + vi[1] * B.w[1] + vi[2] * B.w[2];
+  g.dA = g.d0[0] * B.A0[0] + g.d0[1] * B.A0[1] + g.d0[2] * B.A0[2];
+  g.n4v = 4.0 * (g.n0[0] * vi[0] + g.n0[1] * vi[1] + g.n0[2] * vi[2]);
+  g.nw = g.n0[0] * B.w[0] + g.n0[1] * B.w[1] + g.n0[2] * B.w[2];
+  g.g7 = 3.5 * gM * g.rinv0;
+  const double gm_s = a.G * in.m_s;
+  const S n0s[3] = {-g.n0[0], -g.n0[1], -g.n0[2]};
+  g.ks = gm_s * g.rinv0 * g.rinv0;
+  g.nvs = n0s[0] * vi[0] + n0s[1] * vi[1] + n0s[2] * vi[2];
+  g.nws = n0s[0] * B.w[0] + n0s[1] * B.w[1] + n0s[2] * B.w[2];
+  g.g7s = 3.5 * gm_s * g.rinv0;
+  return g;
+}
+
+// Star k's epilogue from its pair sums: outputs, stage update and next
+// packet.  bh: its term of the massive object's 1PN sum; pro: its block-sum
+// terms of the next prologue.
+template <typename S, typename PkT>
+__device__ __forceinline__ void epi_star(const EpiArgs& a, int k, const EpiStar<S>& in,
+                                         const EpiBh<S>& B, const EpiGeo<S>& g, S (&sum)[kNF],
+                                         S (&bh)[3], double (&pro)[epi_next_terms<PkT>()]) {
+  constexpr bool DUAL = IsDual<S>::value;
+  constexpr bool CHAIN = !std::is_void<PkT>::value;
+  constexpr bool JNEXT = std::is_same<PkT, Dual>::value;  // the jerk sweep's packets
+  static_assert(!CHAIN || !DUAL, "chained epilogues are FP64 evaluations");
+  const int i = k + 1;
+  const double gM = a.G * B.M;
+  const S x0 = B.x0[0], y0 = B.x0[1], z0 = B.x0[2], V0 = B.V0;
+  const S (&A0)[3] = B.A0;
+  const S (&w)[3] = B.w;
+  const S ui = in.u, bx = in.bx, by = in.by, bz = in.bz, xi = in.x, yi = in.y, zi = in.z;
+  const S (&vi)[3] = in.v;
+  sum[F_C2] *= kSqrt32;  // the sweep accumulates D'/sqrt(3/2)
+  // Newtonian part: g_i - b_i with g_i = -G_i
+  const S aN[3] = {-sum[F_G] - bx, -sum[F_G + 1] - by, -sum[F_G + 2] - bz};
+  S Vi = sum[F_U] + ui;  // -phi_i
+  S a1[3] = {0.0, 0.0, 0.0};
+  if (!a.newton_only) {
+    S Vphi = Vi;
+    S aNs[3] = {aN[0], aN[1], aN[2]};
+    if constexpr (!DUAL) {
+      if (a.phi_in) {  // correction mode: the caller's potential and Newtonian acceleration
+        Vphi = -a.phi_in[i];
+        aNs[0] = a.accN_in[3 * i];
+        aNs[1] = a.accN_in[3 * i + 1];
+        aNs[2] = a.accN_in[3 * i + 2];
+      }
     }
-  } else if constexpr (!DUAL && !std::is_void<PkT>::value) {
+    // Eq. (6) star-star terms: S_i0 G_i + Q_i + C2_i v_i + 7 Q7_i, S_i0 = -v_i^2 + 4 u_i
+    const S Si0 = -g.vi2 + 4.0 * ui;
+    S q[3];
+    for (int c = 0; c < 3; ++c)
+      q[c] = Si0 * sum[F_G + c] + sum[F_Q + c] + sum[F_C2] * vi[c] + 7.0 * sum[F_Q7 + c];
+    // massive-object partner (Eq. (5) and the G^2 m M / velocity terms of Eq. (6))
+    const S br = -g.vi2 + 4.0 * g.vw + 4.0 * Vphi + V0 + 0.5 * g.dA;
+    for (int c = 0; c < 3; ++c) {
+      const S pull =
+          g.kk * (br * g.n0[c] + g.n4v * (vi[c] - w[c]) - 3.0 * g.nw * vi[c]) + g.g7 * A0[c];
+      a1[c] = a.lam * (pull + q[c]);
+    }
+    // this star's term of the massive object's 1PN sum (Eqs. (2)-(3))
+    const S n0s[3] = {-g.n0[0], -g.n0[1], -g.n0[2]};
+    const S d0s[3] = {-g.d0[0], -g.d0[1], -g.d0[2]};
+    const S dAs = d0s[0] * aNs[0] + d0s[1] * aNs[1] + d0s[2] * aNs[2];
+    const S brs = -2.0 * g.vi2 + 4.0 * g.vw + 1.5 * g.nvs * g.nvs + 4.0 * V0 + Vphi + 0.5 * dAs;
+    for (int c = 0; c < 3; ++c)
+      bh[c] = g.ks * (brs * n0s[c] + 3.0 * g.nvs * vi[c] - 3.0 * g.nvs * w[c] -
+                      4.0 * g.nws * vi[c]) +
+              g.g7s * aNs[c];
+  }
+  if (a.acc_newton) {
+    a.acc_newton[3 * i] = val(aN[0]);
+    a.acc_newton[3 * i + 1] = val(aN[1]);
+    a.acc_newton[3 * i + 2] = val(aN[2]);
+  }
+  if (a.phi) a.phi[i] = -val(Vi);
+  if (a.acc_1pn) {
+    a.acc_1pn[3 * i] = val(a1[0]);
+    a.acc_1pn[3 * i + 1] = val(a1[1]);
+    a.acc_1pn[3 * i + 2] = val(a1[2]);
+  }
+  const S at[3] = {aN[0] + a1[0], aN[1] + a1[1], aN[2] + a1[2]};
+  if (a.acc_tot) {
+    for (int c = 0; c < 3; ++c) a.acc_tot[3 * i + c] = val(at[c]);
+  }
+  if (!finite_s(at[0]) || !finite_s(at[1]) || !finite_s(at[2])) atomicOr(a.status, 1);
+  if constexpr (DUAL) {
+    if (a.jerk) {
+      for (int c = 0; c < 3; ++c) a.jerk[3 * i + c] = at[c].d;
+    }
+    if (a.herm >= 0) {
+      for (int c = 0; c < 3; ++c) hermite_update(a, 3 * (size_t)i + c, at[c].v, at[c].d);
+    }
+  } else {
+    if constexpr (JNEXT) {
+      // the jerk sweep's prologue terms of this star (as k_prologue<Dual>
+      // computes them from pos_d = vel, vel_d = the acceleration)
+      const Dual x0d[3] = {Dual(x0, a.vel[0]), Dual(y0, a.vel[1]), Dual(z0, a.vel[2])};
+      const Dual xsd[3] = {Dual(xi, vi[0]), Dual(yi, vi[1]), Dual(zi, vi[2])};
+      const Dual vsd[3] = {Dual(vi[0], at[0]), Dual(vi[1], at[1]), Dual(vi[2], at[2])};
+      Dual pd[7];
+      star_terms<Dual, Dual>(x0d, xsd, vsd, in.m_s, a.G, gM, a.eps2, a.pk_next, a.ub_next, k,
+                             pd);
+#pragma unroll
+      for (int q = 0; q < 7; ++q) {
+        pro[q] = pd[q].v;
+        pro[7 + q] = pd[q].d;
+      }
+    }
     if (a.stage >= 0) {
-      for (int c = 0; c < 3; ++c) {
-        bh_x[c] = a.X[c];
-        bh_kx[c] = a.stage == 0 ? 0.0 : a.KX[c];
-        bh_v[c] = a.vel[c];
+      double xn[3] = {0.0, 0.0, 0.0}, vn[3] = {0.0, 0.0, 0.0};
+      for (int c = 0; c < 3; ++c)
+        rk4_update(a, 3 * (size_t)i + c, in.rk[c], vi[c], at[c], xn[c], vn[c]);
+      if constexpr (CHAIN && !JNEXT) {
+        // the massive object's next position, as k_bh_final will compute it
+        double x0n[3];
+        for (int c = 0; c < 3; ++c) x0n[c] = rk4_next(a.stage, a.dt, B.X[c], B.KX[c], B.v[c]);
+        star_terms<PkT, double>(x0n, xn, vn, in.m_s, a.G, gM, a.eps2, a.pk_next, a.ub_next,
+                                k, pro);
       }
     }
   }
-  if (star) {
-    const double* ub = a.ub + 4 * W * (size_t)k;
-    ui = get<S>(ub, 0, 4);
-    bx = get<S>(ub, 1, 4);
-    by = get<S>(ub, 2, 4);
-    bz = get<S>(ub, 3, 4);
-    xi = ld<S>(a.pos, a.pos_d, 3 * i);
-    yi = ld<S>(a.pos, a.pos_d, 3 * i + 1);
-    zi = ld<S>(a.pos, a.pos_d, 3 * i + 2);
-    if (!a.newton_only) {
-      vi[0] = ld<S>(a.vel, a.vel_d, 3 * i);
-      vi[1] = ld<S>(a.vel, a.vel_d, 3 * i + 1);
-      vi[2] = ld<S>(a.vel, a.vel_d, 3 * i + 2);
-      m_s = a.mass[i];
+}
+
+// Block sums of the workgroup's stars, which are in the calling wavefront: it
+// sums (every lane of them then holds every sum) and writes its row of the
+// massive object's 1PN sum and of the next prologue from its registers.
+// COLS > 0: the stars are lanes 0 .. COLS - 1 and rows lie across columns
+// [column][workgroup] (the one-launch stages); 0: up to 64 stars, rows
+// [workgroup][column].
+template <typename S, typename PkT, int COLS>
+__device__ __forceinline__ void epi_rows(const EpiArgs& a, int blk, const S (&bh)[3],
+                                         const double (&pro)[epi_next_terms<PkT>()]) {
+  constexpr int W = Width<S>::n;
+  constexpr bool CHAIN = !std::is_void<PkT>::value;
+  constexpr int NP = epi_next_terms<PkT>();
+  constexpr int NB = CHAIN ? 3 + NP : 3 * W;
+  static_assert(COLS == 0 || (CHAIN && W == 1 && NP == 7), "columns: the Runge-Kutta stages");
+  double bhs[NB];
+#pragma unroll
+  for (int c = 0; c < 3; ++c) put(bhs, c, 3, bh[c]);
+  if constexpr (CHAIN) {
+#pragma unroll
+    for (int q = 0; q < NP; ++q) bhs[3 + q] = pro[q];
+  }
+  const int l = threadIdx.x & 63;
+  if constexpr (COLS > 0) {
+    star_sum<COLS, NB>(bhs);
+    if (l == 0) {
+#pragma unroll
+      for (int c = 0; c < NB; ++c) {
+        if (c < 3) a.bhpart[(size_t)c * a.nbpro + blk] = bhs[c];
+        else a.bpart_next[(size_t)(c - 3) * a.nbpro + blk] = bhs[c];
+      }
     }
-    if constexpr (!DUAL) {
-      for (int c = 0; c < 3; ++c) rk[c] = rk4_load(a, 3 * (size_t)i + c);
+  } else {
+    wave_allsum<NB>(bhs);
+    if (l < 4 * W) {
+      // row layout: values in columns 0..2, derivatives in 4..6 (Dual)
+      const int q = l & 3, h = l >> 2;
+      a.bhpart[(size_t)blk * 4 * W + l] = q < 3 ? pick(bhs, h * 3 + q) : 0.0;
+    }
+    if constexpr (CHAIN) {
+      // the prologue's row layout: sum m b (3), sum m u, sum m v (3), 0 (and
+      // the same 8 columns of derivatives for the jerk sweep)
+      constexpr int RW = NP == 14 ? 16 : 8;
+      if (l >= 32 && l < 32 + RW) {
+        const int c = l - 32, q = c & 7, h = c >> 3;
+        a.bpart_next[(size_t)blk * RW + c] = q < 7 ? pick(bhs, 3 + h * 7 + q) : 0.0;
+      }
     }
   }
+}
+
+// The epilogue of kEpiStars stars (blk * kEpiStars ...) from the splits'
+// partial sums; fsum: kNF W kEpiStars doubles of LDS.
+template <typename S, typename PkT = void>
+__device__ __forceinline__ void epilogue_block(const EpiArgs& a, int blk, double* fsum) {
+  constexpr bool DUAL = IsDual<S>::value;
+  constexpr int W = DUAL ? 2 : 1;
+  constexpr int NFO = kNF * W;
+  static_assert(kEpiStars == 64, "the stars of a workgroup are in its first wavefront");
+  // Every global read of the workgroup is requested before the first wait:
+  // the prologue rows, the pair partials, the star's own inputs and
+  // Runge-Kutta state, the massive object's state.  (At small N this kernel is
+  // a chain of memory latencies; issued in order, they added up.)
+  double rows[bh_cols<S>()];
+  rows_load<bh_cols<S>()>(a.bpart, a.nbpro, DUAL ? 16 : 8, rows);
+  EpiBh<S> B;
+  B.M = a.mass[0];
+  for (int c = 0; c < 3; ++c) B.x0[c] = ld<S>(a.pos, a.pos_d, c);
+  // the massive object's step-start position, stage sum and velocity (uniform:
+  // scalar loads)
+  if constexpr (!DUAL && !std::is_void<PkT>::value) {
+    if (a.stage >= 0) {
+      for (int c = 0; c < 3; ++c) {
+        B.X[c] = a.X[c];
+        B.KX[c] = a.stage == 0 ? 0.0 : a.KX[c];
+        B.v[c] = a.vel[c];
+      }
+    }
+  }
+  const int k = blk * kEpiStars + threadIdx.x;
+  const bool star = threadIdx.x < kEpiStars && k < a.Ns;
+  EpiStar<S> in;
+  if (star) in = epi_star_load<S>(a, k);
 
   // split reduction: thread (g, l) sums fields g, g+4, g+8, ... of star l, in
   // split order; the loads of up to 8 (dual: 4) splits of all its fields are
   // issued together, then added in order
-  if constexpr (!OWNBH) {
+  {
     constexpr int FPT = (NFO + 3) / 4;      // fields per thread
     constexpr int BATCH = DUAL ? 4 : 8;     // splits per batch of loads
     const int g = threadIdx.x >> 6, l = threadIdx.x & 63;
@@ -1171,190 +1383,45 @@ __device__ __forceinline__ void epilogue_rows(const EpiArgs& a, int blk, double*
         if (g + 4 * fi < NFO) fsum[(g + 4 * fi) * kEpiStars + l] = sum[fi];
     }
   }
-  if constexpr (!OWNBH) __syncthreads();  // fsum complete (the caller orders its own)
-  S A0[3], V0, P[3];
-  bh_quantities<S>(a, rows, A0, V0, P);
-  const double gM = a.G * M;
-  const double iM = 1.0 / M;
-  const S w[3] = {-(P[0] * iM), -(P[1] * iM), -(P[2] * iM)};
+  __syncthreads();  // fsum complete
+  S P[3];
+  bh_quantities<S>(a, rows, B.A0, B.V0, P);
+  const double iM = 1.0 / B.M;
+  for (int c = 0; c < 3; ++c) B.w[c] = -(P[c] * iM);
 
-  constexpr bool CHAIN = !std::is_void<PkT>::value;
-  constexpr bool JNEXT = std::is_same<PkT, Dual>::value;  // the jerk sweep's packets
-  constexpr int NP = JNEXT ? 14 : 7;  // block-sum terms of the next prologue
-  static_assert(!CHAIN || !DUAL, "chained epilogues are FP64 evaluations");
   S bh[3] = {0.0, 0.0, 0.0};
-  double pro[NP];
+  double pro[epi_next_terms<PkT>()];
 #pragma unroll
-  for (int q = 0; q < NP; ++q) pro[q] = 0.0;
+  for (int q = 0; q < epi_next_terms<PkT>(); ++q) pro[q] = 0.0;
   if (star) {
     const int t = threadIdx.x;
     S sum[kNF];
 #pragma unroll
     for (int f = 0; f < kNF; ++f) {
-      if constexpr (DUAL) sum[f] = S(fsum[f * NSTAR + t], fsum[(kNF + f) * NSTAR + t]);
-      else sum[f] = fsum[f * NSTAR + t];
+      if constexpr (DUAL) sum[f] = S(fsum[f * kEpiStars + t], fsum[(kNF + f) * kEpiStars + t]);
+      else sum[f] = fsum[f * kEpiStars + t];
     }
-    sum[F_C2] *= kSqrt32;  // the sweep accumulates D'/sqrt(3/2)
-    // Newtonian part: g_i - b_i with g_i = -G_i
-    const S aN[3] = {-sum[F_G] - bx, -sum[F_G + 1] - by, -sum[F_G + 2] - bz};
-    S Vi = sum[F_U] + ui;  // -phi_i
-    S a1[3] = {0.0, 0.0, 0.0};
-    if (!a.newton_only) {
-      const S vi2 = vi[0] * vi[0] + vi[1] * vi[1] + vi[2] * vi[2];
-      S Vphi = Vi;
-      S aNs[3] = {aN[0], aN[1], aN[2]};
-      if constexpr (!DUAL) {
-        if (a.phi_in) {  // correction mode: the caller's potential and Newtonian acceleration
-          Vphi = -a.phi_in[i];
-          aNs[0] = a.accN_in[3 * i];
-          aNs[1] = a.accN_in[3 * i + 1];
-          aNs[2] = a.accN_in[3 * i + 2];
-        }
-      }
-      // Eq. (6) star-star terms: S_i0 G_i + Q_i + C2_i v_i + 7 Q7_i, S_i0 = -v_i^2 + 4 u_i
-      const S Si0 = -vi2 + 4.0 * ui;
-      S q[3];
-      for (int c = 0; c < 3; ++c)
-        q[c] = Si0 * sum[F_G + c] + sum[F_Q + c] + sum[F_C2] * vi[c] + 7.0 * sum[F_Q7 + c];
-      // massive-object partner (Eq. (5) and the G^2 m M / velocity terms of Eq. (6))
-      const S d0[3] = {xi - x0, yi - y0, zi - z0};
-      const S rinv0 = rsqrt_t(d0[0] * d0[0] + d0[1] * d0[1] + d0[2] * d0[2] + a.eps2);
-      const S n0[3] = {d0[0] * rinv0, d0[1] * rinv0, d0[2] * rinv0};
-      const S kk = gM * rinv0 * rinv0;
-      const S vw = vi[0] * w[0] + vi[1] * w[1] + vi[2] * w[2];
-      const S dA = d0[0] * A0[0] + d0[1] * A0[1] + d0[2] * A0[2];
-      const S br = -vi2 + 4.0 * vw + 4.0 * Vphi + V0 + 0.5 * dA;
-      const S n4v = 4.0 * (n0[0] * vi[0] + n0[1] * vi[1] + n0[2] * vi[2]);
-      const S nw = n0[0] * w[0] + n0[1] * w[1] + n0[2] * w[2];
-      const S g7 = 3.5 * gM * rinv0;
-      for (int c = 0; c < 3; ++c) {
-        const S B = kk * (br * n0[c] + n4v * (vi[c] - w[c]) - 3.0 * nw * vi[c]) + g7 * A0[c];
-        a1[c] = a.lam * (B + q[c]);
-      }
-      // this star's term of the massive object's 1PN sum (Eqs. (2)-(3))
-      const S Vs = Vphi;
-      const double gm_s = a.G * m_s;
-      const S ks = gm_s * rinv0 * rinv0;
-      const S n0s[3] = {-n0[0], -n0[1], -n0[2]};
-      const S d0s[3] = {-d0[0], -d0[1], -d0[2]};
-      const S nvs = n0s[0] * vi[0] + n0s[1] * vi[1] + n0s[2] * vi[2];
-      const S dAs = d0s[0] * aNs[0] + d0s[1] * aNs[1] + d0s[2] * aNs[2];
-      const S brs = -2.0 * vi2 + 4.0 * vw + 1.5 * nvs * nvs + 4.0 * V0 + Vs + 0.5 * dAs;
-      const S nws = n0s[0] * w[0] + n0s[1] * w[1] + n0s[2] * w[2];
-      const S g7s = 3.5 * gm_s * rinv0;
-      for (int c = 0; c < 3; ++c)
-        bh[c] = ks * (brs * n0s[c] + 3.0 * nvs * vi[c] - 3.0 * nvs * w[c] - 4.0 * nws * vi[c]) +
-                g7s * aNs[c];
-    }
-    if (a.acc_newton) {
-      a.acc_newton[3 * i] = val(aN[0]);
-      a.acc_newton[3 * i + 1] = val(aN[1]);
-      a.acc_newton[3 * i + 2] = val(aN[2]);
-    }
-    if (a.phi) a.phi[i] = -val(Vi);
-    if (a.acc_1pn) {
-      a.acc_1pn[3 * i] = val(a1[0]);
-      a.acc_1pn[3 * i + 1] = val(a1[1]);
-      a.acc_1pn[3 * i + 2] = val(a1[2]);
-    }
-    const S at[3] = {aN[0] + a1[0], aN[1] + a1[1], aN[2] + a1[2]};
-    if (a.acc_tot) {
-      for (int c = 0; c < 3; ++c) a.acc_tot[3 * i + c] = val(at[c]);
-    }
-    if (!finite_s(at[0]) || !finite_s(at[1]) || !finite_s(at[2])) atomicOr(a.status, 1);
-    if constexpr (DUAL) {
-      if (a.jerk) {
-        for (int c = 0; c < 3; ++c) a.jerk[3 * i + c] = at[c].d;
-      }
-      if (a.herm >= 0) {
-        for (int c = 0; c < 3; ++c) hermite_update(a, 3 * (size_t)i + c, at[c].v, at[c].d);
-      }
-    } else {
-      if constexpr (JNEXT) {
-        // the jerk sweep's prologue terms of this star (as k_prologue<Dual>
-        // computes them from pos_d = vel, vel_d = the acceleration)
-        const Dual x0d[3] = {Dual(x0, a.vel[0]), Dual(y0, a.vel[1]), Dual(z0, a.vel[2])};
-        const Dual xsd[3] = {Dual(xi, vi[0]), Dual(yi, vi[1]), Dual(zi, vi[2])};
-        const Dual vsd[3] = {Dual(vi[0], at[0]), Dual(vi[1], at[1]), Dual(vi[2], at[2])};
-        Dual pd[7];
-        star_terms<Dual, Dual>(x0d, xsd, vsd, a.mass[i], a.G, gM, a.eps2, a.pk_next, a.ub_next, k,
-                               pd);
-#pragma unroll
-        for (int q = 0; q < 7; ++q) {
-          pro[q] = pd[q].v;
-          pro[7 + q] = pd[q].d;
-        }
-      }
-      if (a.stage >= 0) {
-        double xn[3] = {0.0, 0.0, 0.0}, vn[3] = {0.0, 0.0, 0.0};
-        for (int c = 0; c < 3; ++c)
-          rk4_update(a, 3 * (size_t)i + c, rk[c], vi[c], at[c], xn[c], vn[c]);
-        if constexpr (CHAIN && !JNEXT) {
-          // the massive object's next position, as k_bh_final will compute it
-          double x0n[3];
-          for (int c = 0; c < 3; ++c) x0n[c] = rk4_next(a.stage, a.dt, bh_x[c], bh_kx[c], bh_v[c]);
-          star_terms<PkT, double>(x0n, xn, vn, a.mass[i], a.G, gM, a.eps2, a.pk_next, a.ub_next,
-                                  k, pro);
-        }
-      }
-    }
+    epi_star<S, PkT>(a, k, in, B, epi_geo<S>(a, in, B), sum, bh, pro);
   }
-  constexpr int NB = CHAIN ? 3 + NP : 3 * W;
-  double bhs[NB];
-#pragma unroll
-  for (int c = 0; c < 3; ++c) put(bhs, c, 3, bh[c]);
-  if constexpr (CHAIN) {
-#pragma unroll
-    for (int q = 0; q < NP; ++q) bhs[3 + q] = pro[q];
-  }
-  // the stars are in wavefront 0: it sums its rows (wave_allsum, every lane
-  // then holds every sum) and writes them from its registers
-  if (wave_id() == 0) {
-    wave_allsum<NB>(bhs);
-    const int l = threadIdx.x;
-    if (l < 4 * W) {
-      // row layout: values in columns 0..2, derivatives in 4..6 (Dual)
-      const int q = l & 3, h = l >> 2;
-      a.bhpart[(size_t)blk * 4 * W + l] = q < 3 ? pick(bhs, h * 3 + q) : 0.0;
-    }
-    if constexpr (CHAIN) {
-      // the prologue's row layout: sum m b (3), sum m u, sum m v (3), 0 (and
-      // the same 8 columns of derivatives for the jerk sweep)
-      constexpr int RW = JNEXT ? 16 : 8;
-      if (l >= 32 && l < 32 + RW) {
-        const int c = l - 32, q = c & 7, h = c >> 3;
-        a.bpart_next[(size_t)blk * RW + c] = q < 7 ? pick(bhs, 3 + h * 7 + q) : 0.0;
-      }
-    }
-  }
-}
-
-template <typename S, typename PkT = void>
-__device__ __forceinline__ void epilogue_block(const EpiArgs& a, int blk, double* lds,
-                                               double* fsum) {
-  double rows[bh_cols<S>()];
-  rows_load<bh_cols<S>()>(a.bpart, a.nbpro, IsDual<S>::value ? 16 : 8, rows);
-  epilogue_rows<S, PkT, kEpiStars, false>(a, blk, lds, fsum, rows, BhStage{});
+  if (wave_id() == 0) epi_rows<S, PkT, 0>(a, blk, bh, pro);
 }
 
 template <typename S>
 __global__ __launch_bounds__(kBlock) void k_epilogue(EpiArgs a) {
-  __shared__ double lds[(IsDual<S>::value ? 16 : 7) * kBlock];
   __shared__ double fsum[kNF * Width<S>::n * kEpiStars];
-  epilogue_block<S>(a, blockIdx.x, lds, fsum);
+  epilogue_block<S>(a, blockIdx.x, fsum);
 }
 
 // FP64 epilogue that also performs the next sweep's prologue (packets of
 // PkOf<T>; T = Dual: the jerk sweep at this state), saving that kernel.
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_epilogue_chain(EpiArgs a) {
-  __shared__ double lds[(std::is_same<T, Dual>::value ? 17 : 10) * kBlock];
   __shared__ double fsum[kNF * kEpiStars];
-  epilogue_block<double, T>(a, blockIdx.x, lds, fsum);
+  epilogue_block<double, T>(a, blockIdx.x, fsum);
 }
 
 template <typename S>
-__device__ __forceinline__ void bh_final_block(const EpiArgs& a, double* lds) {
+__device__ __forceinline__ void bh_final_block(const EpiArgs& a) {
   constexpr bool DUAL = IsDual<S>::value;
   constexpr int W = DUAL ? 2 : 1;
   // both row sets and the massive object's own state are requested before
@@ -1405,8 +1472,7 @@ __device__ __forceinline__ void bh_final_block(const EpiArgs& a, double* lds) {
 
 template <typename S>
 __global__ __launch_bounds__(kBlock) void k_bh_final(EpiArgs a) {
-  __shared__ double lds[(IsDual<S>::value ? 16 : 7) * kBlock];
-  bh_final_block<S>(a, lds);
+  bh_final_block<S>(a);
 }
 
 // The jerk evaluation's dual epilogue with the FP64 pass's massive-object
@@ -1414,13 +1480,12 @@ __global__ __launch_bounds__(kBlock) void k_bh_final(EpiArgs a) {
 // epilogue reads neither the massive object's FP64 acceleration nor the FP64
 // partial rows (its own rows are in separate buffers).
 __global__ __launch_bounds__(kBlock) void k_epilogue_dual_bh(EpiArgs a, EpiArgs e) {
-  __shared__ double lds[16 * kBlock];
   __shared__ double fsum[kNF * 2 * kEpiStars];
   if (blockIdx.x == gridDim.x - 1) {
-    bh_final_block<double>(e, lds);
+    bh_final_block<double>(e);
     return;
   }
-  epilogue_block<Dual>(a, blockIdx.x, lds, fsum);
+  epilogue_block<Dual>(a, blockIdx.x, fsum);
 }
 
 // The sweep of a chained Runge-Kutta stage with the previous stage's
@@ -1428,64 +1493,327 @@ __global__ __launch_bounds__(kBlock) void k_epilogue_dual_bh(EpiArgs a, EpiArgs 
 // reads only star packets, which the previous epilogue has written, so the
 // two are independent and the stage saves a kernel boundary.  Grid: the
 // sweep's (iblocks + 1) x nsplit; column iblocks, split 0 runs the update
-// (sharing the sweep's LDS), the rest of that column exits.
+// the rest of that column exits.
 template <typename T, int MODE, int IPT, int WS>
 __global__ __launch_bounds__(pair_threads<WS>()) void k_pair_bh(PairArgs a, EpiArgs e) {
-  constexpr int L = pair_red_doubles<T, IPT, WS>() > 7 * kBlock ? pair_red_doubles<T, IPT, WS>()
-                                                                : 7 * kBlock;
-  __shared__ double lds[L];
+  __shared__ double red[pair_red_doubles<T, IPT, WS>()];
   if (blockIdx.x == gridDim.x - 1) {
-    if (blockIdx.y == 0) bh_final_block<double>(e, lds);
+    if (blockIdx.y == 0) bh_final_block<double>(e);
     return;
   }
-  pair_block<T, MODE, IPT, WS>(a, blockIdx.x, blockIdx.y, lds);
+  pair_block<T, MODE, IPT, WS>(a, blockIdx.x, blockIdx.y, red);
 }
 
 // ---------------------------------------------------------------------------
-// Small systems: one launch per Runge-Kutta stage.  With a few hundred bodies
-// a stage is a chain of latencies (launch, loads, reductions, dependent FP64
-// arithmetic) rather than work, and one kernel per stage saves a launch and
-// the split partials' trip through memory: a workgroup owns NS stars and
-// sums all their j in its own 256 lanes (lane sl + NS q takes star sl and
-// j = q, q + 256/NS, ...), reduces them in fixed order (a butterfly within
-// each wavefront, then the four wavefronts) and runs those stars' epilogue.  No other workgroup's partials are needed, so
-// nothing waits across workgroups.  The massive object's update of the
-// previous stage needs every epilogue's rows; each workgroup computes it
-// itself from the rows the previous launch wrote (the same sums in the same
-// order, so the same bits everywhere), and workgroup 0 stores it.  Every
-// buffer a stage reads is one no workgroup of that stage writes: packets, u/b
-// rows and massive-object 1PN rows alternate between two buffers, block rows
-// rotate through four (a stage reads its own and the previous stage's), and
-// the massive object's state alternates between two copies of
-// (X, V, Xs, Vs, KX, KV).
+// Small systems: one launch per Runge-Kutta stage.  Such a stage is a chain of
+// latencies (launch, loads, reductions, dependent FP64 arithmetic) rather than
+// work: one kernel per stage saves a launch and the split partials' trip
+// through memory.  A workgroup owns NS stars.  Its first kStageWaves
+// wavefronts sum all their j (lane sl + NS q takes star sl and j = q,
+// q + 64 kStageWaves / NS, ...), reduce them in fixed order (exchanges within
+// each wavefront, then the wavefronts).  No other workgroup's partials are
+// needed, so nothing waits across workgroups.  One more wavefront meanwhile
+// loads the stars' own inputs and prepares what their epilogue needs of the
+// massive object: its update of the previous stage needs every epilogue's
+// rows, and each workgroup computes it itself from the rows the previous
+// launch wrote (the same sums in the same order, so the same bits everywhere);
+// workgroup 0 stores it.  That wavefront then runs the stars' epilogue.  Rows
+// lie across columns, so that its loads are contiguous.  Where every lane has
+// one j at most (DIRECT) it loads that packet itself; else the packets pass
+// through LDS, kStageTile at a time, copied by direct loads that are all in
+// flight at once.
+// A stage of 100 stars (2 per workgroup), in us from its first instruction:
+// the massive object's loads back at 1.6, its sums 1.9, its update 2.5 (the
+// sweep done at 1.5), the epilogue 4.9, its rows 5.1, the next launch 6.3.
+// 1024 stars (4 per workgroup): packets in LDS 1.9, swept 5.6, epilogue 9.0.
+// Against two wavefronts' sweep with the epilogue and the update after it, in
+// us per RK4 step: 34.6 -> 21.8 (100 stars), 40.0 -> 26.4 (300), and 50.8
+// (the two-kernel stages) -> 37.0 (1024).
+// Every buffer a stage reads is one no workgroup of that stage writes:
+// packets, u/b rows, block rows, massive-object 1PN rows and the massive
+// object's state (X, V, Xs, Vs, KX, KV and its last Newtonian acceleration)
+// alternate between two buffers.
 // ---------------------------------------------------------------------------
 constexpr int kStageFirst = 0;  // the first stage of a call: no pending update
 constexpr int kStageFull = 1;   // pending update, sweep and epilogue
 constexpr int kStageFinal = 2;  // the last pending update only (one workgroup)
+constexpr int kStageWaves = 8;  // wavefronts of the sweep
+constexpr int kStageThreads = 64 * (kStageWaves + 1);
+constexpr int kStageTile = 1024;  // packets in LDS
 
 struct StageArgs {
-  EpiArgs e;             // this stage's epilogue; e.nbpro rows in every row buffer
+  EpiArgs e;             // this stage's epilogue; e.nbpro workgroups (rows in every row buffer)
   const void* pk;        // this stage's packets (PkOf<T>)
   int mode;
   int pstage;            // stage of the pending massive-object update
-  const double* prow;    // its block rows [e.nbpro][8]
-  const double* phrow;   // its massive-object 1PN rows [e.nbpro][4]
-  const double* bhs_in;  // the massive object's X, V, Xs, Vs, KX, KV before that update
-  double* bhs_out;       // ... after it
+  const double* phrow;   // that stage's massive-object 1PN rows [3][e.nbpro]
+  // the massive object's X, V, Xs, Vs, KX, KV before that update, and its
+  // Newtonian acceleration at that stage; the same after it, at this stage
+  const double* bhs_in;
+  double* bhs_out;
 };
+constexpr int kBhState = 21;
 
-// The stars' pair sums of one workgroup (lanes of star sl: sl + NS q).
-template <typename T, int NS>
-__device__ __forceinline__ void stage_sweep(const StageArgs& sa, double (&acc)[kNF][1]) {
+// Column sums, this lane's part: rows l, l + 64, ... of K columns of n rows, in
+// order; the loads of several rows are in flight together.
+template <int K>
+__device__ __forceinline__ void cols_load(const double* part, int n, double* v) {
+  const int l = threadIdx.x & 63;
+#pragma unroll
+  for (int k = 0; k < K; ++k) v[k] = part[(size_t)k * n + min(l, n - 1)];
+  if (l >= n) {
+#pragma unroll
+    for (int k = 0; k < K; ++k) v[k] = 0.0;
+  }
+  constexpr int U = 2;
+  for (int r = l + 64; r - l < n; r += U * 64) {
+    double w[U][K];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int k = 0; k < K; ++k) w[u][k] = part[(size_t)k * n + min(r + 64 * u, n - 1)];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int k = 0; k < K; ++k) v[k] += r + 64 * u < n ? w[u][k] : 0.0;
+  }
+}
+
+// Two values folded into one register of sums: the lanes with bit M clear end
+// with x[i] + x[i ^ M], those with it set with the same sum of y (M = 32, 16: by
+// a swap of halves or rows; 8, 4: by DPP moves within rows, written to the banks
+// of four lanes that lack the value).  Reducing K values over a wavefront this
+// way takes about as many additions as there are values, where summing each of
+// them in all lanes takes one per value and level.
+template <int M>
+__device__ __forceinline__ double fold(double x, double y) {
+  const unsigned long long ux = __builtin_bit_cast(unsigned long long, x);
+  const unsigned long long uy = __builtin_bit_cast(unsigned long long, y);
+  const unsigned xl = (unsigned)ux, xh = (unsigned)(ux >> 32);
+  const unsigned yl = (unsigned)uy, yh = (unsigned)(uy >> 32);
+  unsigned al, ah, bl, bh;
+  if constexpr (M == 32) {
+    const auto l = __builtin_amdgcn_permlane32_swap(xl, yl, false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap(xh, yh, false, false);
+    al = l[0], bl = l[1], ah = h[0], bh = h[1];
+  } else if constexpr (M == 16) {
+    const auto l = __builtin_amdgcn_permlane16_swap(xl, yl, false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap(xh, yh, false, false);
+    al = l[0], bl = l[1], ah = h[0], bh = h[1];
+  } else {
+    // a: x, with y shifted up by M in the lanes with bit M set; b: y, with x
+    // shifted down in the others
+    constexpr int set = M == 8 ? 0xC : 0xA, clear = M == 8 ? 0x3 : 0x5;
+    al = __builtin_amdgcn_update_dpp((int)xl, (int)yl, 0x110 + M, 0xF, set, false);
+    ah = __builtin_amdgcn_update_dpp((int)xh, (int)yh, 0x110 + M, 0xF, set, false);
+    bl = __builtin_amdgcn_update_dpp((int)yl, (int)xl, 0x100 + M, 0xF, clear, false);
+    bh = __builtin_amdgcn_update_dpp((int)yh, (int)xh, 0x100 + M, 0xF, clear, false);
+  }
+  return __builtin_bit_cast(double, ((unsigned long long)ah << 32) | al) +
+         __builtin_bit_cast(double, ((unsigned long long)bh << 32) | bl);
+}
+
+// Twelve values reduced over the lanes that are NS apart: the lane's results
+// r[0 .. fold_regs - 1] are the sums of the values f[0 ..] of residue lane % NS
+// (f = -1: a copy of another lane's).
+template <int NS>
+constexpr int fold_regs() { return NS >= 16 ? 3 : NS == 8 ? 2 : 1; }
+template <int NS>
+__device__ __forceinline__ void fold12(const double (&x)[12], double (&r)[fold_regs<NS>()],
+                                       int (&f)[fold_regs<NS>()]) {
+  const int lane = threadIdx.x & 63;
+  const int row = (lane >> 4 & 1) * 2 + (lane >> 5);  // which of four values a row of 16 holds
+  double z[3];
+#pragma unroll
+  for (int i = 0; i < 3; ++i)
+    z[i] = fold<16>(fold<32>(x[4 * i], x[4 * i + 1]), fold<32>(x[4 * i + 2], x[4 * i + 3]));
+  if constexpr (NS >= 16) {
+#pragma unroll
+    for (int i = 0; i < 3; ++i) r[i] = z[i], f[i] = 4 * i + row;
+  } else {
+    const int b8 = lane >> 3 & 1;
+    const double u = fold<8>(z[0], z[1]), w = z[2] + dpp_d<0x128>(z[2]);
+    if constexpr (NS == 8) {
+      r[0] = u, f[0] = 4 * b8 + row;
+      r[1] = w, f[1] = b8 ? -1 : 8 + row;
+    } else {
+      const int b4 = lane >> 2 & 1;
+      r[0] = fold<4>(u, w);
+      f[0] = !b4 ? 4 * b8 + row : b8 ? -1 : 8 + row;
+      if constexpr (NS == 2) {
+        r[0] += dpp_d<0x4E>(r[0]);  // lane ^ 2
+        if (lane & 2) f[0] = -1;
+      }
+    }
+  }
+}
+
+// Ten values summed over a wavefront, as scalars.
+__device__ __forceinline__ void sum10(double (&v)[10]) {
+  const double x[12] = {v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7], v[8], v[9], 0.0, 0.0};
+  double r[1];
+  int f[1];
+  fold12<2>(x, r, f);
+  r[0] += dpp_d<0xB1>(r[0]);  // lane ^ 1: every lane now holds the whole sum of its value
+#pragma unroll
+  for (int k = 0; k < 10; ++k) {
+    // a lane that holds value k: row of 16 by k % 4, then 8 or 4 by k / 4
+    const int lane = (k & 1) * 32 + (k >> 1 & 1) * 16 + (k < 4 ? 0 : k < 8 ? 8 : 4);
+    const unsigned long long u = __builtin_bit_cast(unsigned long long, r[0]);
+    const unsigned lo = __builtin_amdgcn_readlane((int)(unsigned)u, lane);
+    const unsigned hi = __builtin_amdgcn_readlane((int)(unsigned)(u >> 32), lane);
+    v[k] = __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+  }
+}
+
+// The pending update: the massive object's acceleration at stage sa.pstage (as
+// k_bh_final), from its Newtonian part bi[18..20] and the sums of its 1PN rows,
+// then its Runge-Kutta bookkeeping (as rk4_update) on the state in bi, which
+// becomes the state of this stage's evaluation.  Workgroup 0 stores the new
+// step-start state after stage 3.
+__device__ __forceinline__ void stage_bh_update(const StageArgs& sa, const double* sums1,
+                                                double (&bi)[kBhState]) {
+  const EpiArgs& a = sa.e;
+  const int ps = sa.pstage;
+  bool finite = true;
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    const double atc = bi[18 + c] + a.lam * sums1[c];
+    finite = finite && isfinite(atc);
+    const double X = bi[c], V = bi[3 + c], vs = bi[9 + c], KX = bi[12 + c], KV = bi[15 + c];
+    const double xn = rk4_next(ps, a.dt, X, KX, vs);
+    const double vn = rk4_next(ps, a.dt, V, KV, atc);
+    bi[6 + c] = xn;
+    bi[9 + c] = vn;
+    if (ps < 3) {
+      bi[12 + c] = ps == 0 ? vs : KX + 2.0 * vs;
+      bi[15 + c] = ps == 0 ? atc : KV + 2.0 * atc;
+    } else {
+      bi[c] = xn;
+      bi[3 + c] = vn;
+      bi[12 + c] = 0.0;
+      bi[15 + c] = 0.0;
+    }
+  }
+  if (blockIdx.x == 0) {
+    const int l = threadIdx.x & 63;
+    if (l == 0 && !finite) atomicOr(a.status, 1);
+    if (ps == 3) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        if (l == 32 + c) uniform_ptr(a.X)[c] = bi[c];
+        if (l == 40 + c) uniform_ptr(a.V)[c] = bi[3 + c];
+      }
+    }
+  }
+}
+
+// epi_star_load of a Runge-Kutta stage, without a branch: every load in flight
+// together (the stage sums, too, where a stage has none yet).
+__device__ __forceinline__ EpiStar<double> stage_star_load(const EpiArgs& a, int k) {
+  const size_t i = (size_t)k + 1;
+  const double* ub = a.ub + 4 * (size_t)k;
+  EpiStar<double> in;
+  in.u = ub[0], in.bx = ub[1], in.by = ub[2], in.bz = ub[3];
+  in.x = a.pos[3 * i], in.y = a.pos[3 * i + 1], in.z = a.pos[3 * i + 2];
+  in.m_s = a.mass[i];
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    const size_t o = 3 * i + c;
+    in.v[c] = a.vel[o];
+    in.rk[c].X = a.X[o], in.rk[c].V = a.V[o], in.rk[c].KX = a.KX[o], in.rk[c].KV = a.KV[o];
+  }
+  return in;
+}
+
+template <typename T, int NS, bool DIRECT>
+__global__ __launch_bounds__(kStageThreads) void k_stage(StageArgs sa) {
   using Pk = typename PkOf<T>::type;
-  constexpr int Q = kBlock / NS;
+  constexpr int Q = 64 * kStageWaves / NS;  // lanes per star
+  static_assert(sizeof(Pk) % 16 == 0, "copied in 16-byte words");
+  static_assert(kStageTile / Q <= kTile || sizeof(T) == 8, "terms per FP32 partial sum");
+  // (64 words more: the last wavefront's copy may run past the tile)
+  __shared__ __align__(16) char tile[DIRECT ? 16 : (kStageTile * sizeof(Pk) + 64 * 16)];
+  __shared__ double red[kNF * kStageWaves * NS];
+  __shared__ double fsum[kNF * NS];
+  const EpiArgs& a = sa.e;
+  const int lane = threadIdx.x & 63, wave = wave_id();
+  const bool eval = sa.mode != kStageFinal;
+
+  if (wave == kStageWaves) {
+    // the massive object and the stars' epilogue; every global read is
+    // requested before the first wait
+    const bool pend = sa.mode != kStageFirst;
+    const int nb = a.nbpro;
+    const int k = blockIdx.x * NS + lane;
+    const bool star = lane < NS && k < a.Ns;
+    // (this chain is what the launch waits for, the sweep is not)
+    __builtin_amdgcn_s_setprio(3);
+    double v[10], bi[kBhState];  // row sums: 1PN of the pending stage (3), this stage's (7)
+    EpiBh<double> B;
+    EpiStar<double> in = stage_star_load(a, min(k, a.Ns - 1));
+#pragma unroll
+    for (int c = 0; c < kBhState; ++c) bi[c] = sa.bhs_in[c];
+    B.M = a.mass[0];
+    cols_load<3>(sa.phrow, nb, v);  // (read, not used, where nothing is pending)
+    cols_load<7>(a.bpart, nb, v + 3);
+    if (a.stage == 0) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c) in.rk[c].KX = in.rk[c].KV = 0.0;
+    }
+    if (eval && !DIRECT) {  // the tiles' barriers
+      for (int j0 = 0; j0 < a.Ns; j0 += kStageTile) {
+        if (j0 > 0) __syncthreads();
+        __syncthreads();
+      }
+    }
+    sum10(v);
+    const double iM = 1.0 / B.M;
+    if (pend) stage_bh_update(sa, v, bi);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      B.x0[c] = bi[6 + c];
+      bi[18 + c] = B.A0[c] = v[3 + c] * iM;
+      B.w[c] = -(v[7 + c] * iM);
+      B.X[c] = bi[c];
+      B.KX[c] = a.stage == 0 ? 0.0 : bi[12 + c];
+      B.v[c] = bi[9 + c];
+    }
+    B.V0 = v[6] * iM;
+    if (blockIdx.x == 0 && lane < kBhState) sa.bhs_out[lane] = pick(bi, lane);
+    if (!eval) return;
+    EpiGeo<double> g = epi_geo<double>(a, in, B);
+    // held here: otherwise the compiler moves them behind the wait
+    asm volatile("" : "+v"(g.vi2), "+v"(g.kk), "+v"(g.vw), "+v"(g.dA), "+v"(g.n4v), "+v"(g.nw),
+                 "+v"(g.g7), "+v"(g.n0[0]), "+v"(g.n0[1]), "+v"(g.n0[2]));
+    asm volatile("" : "+v"(g.ks), "+v"(g.nvs), "+v"(g.nws), "+v"(g.g7s));
+    __syncthreads();  // the sweep's sums are in red
+    for (int e = lane; e < kNF * NS; e += 64) {  // field e / NS of star e % NS
+      const double* r = red + e / NS * kStageWaves * NS + e % NS;
+      double x = r[0];
+#pragma unroll
+      for (int w = 1; w < kStageWaves; ++w) x += r[w * NS];
+      fsum[e] = x;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // fsum, within this wavefront
+    double bh[3] = {0.0, 0.0, 0.0}, pro[7] = {0, 0, 0, 0, 0, 0, 0};
+    if (star) {
+      double sum[kNF];
+#pragma unroll
+      for (int f = 0; f < kNF; ++f) sum[f] = fsum[f * NS + lane];
+      epi_star<double, T>(a, k, in, B, g, sum, bh, pro);
+    }
+    epi_rows<double, T, NS>(a, blockIdx.x, bh, pro);
+    return;
+  }
+
+  if (!eval) return;
   const Pk* __restrict__ pk = static_cast<const Pk*>(sa.pk);
-  const int Ns = sa.e.Ns;
   const int sl = threadIdx.x % NS, q = threadIdx.x / NS;
   PairI<T, 1> I;
   I.idx[0] = blockIdx.x * NS + sl;
   {
-    const Pk& p = pk[min(I.idx[0], Ns - 1)];  // lanes past the end compute on a copy, never stored
+    const Pk& p = pk[min(I.idx[0], a.Ns - 1)];  // lanes past the end compute on a copy, never stored
     I.x[0] = p.x;
     I.y[0] = p.y;
     I.z[0] = p.z;
@@ -1493,159 +1821,63 @@ __device__ __forceinline__ void stage_sweep(const StageArgs& sa, double (&acc)[k
     I.ky[0] = T(PairScale<T>::k) * (T)p.svy;
     I.kz[0] = T(PairScale<T>::k) * (T)p.svz;
   }
-  const T eps2 = (T)sa.e.eps2;
+  const T eps2 = (T)a.eps2;
+  double acc[kNF][1];
 #pragma unroll
   for (int f = 0; f < kNF; ++f) acc[f][0] = 0.0;
-  PairAcc<T, 1> A;
-  int j = q;
-  while (j < Ns) {
-    // FP32: partial sums over kTile of this lane's terms, then into FP64
-    const int jend = sizeof(T) == 4 ? min(Ns, j + kTile * Q) : Ns;
-    A.zero();
-    for (; j + Q < jend; j += 2 * Q) {
-      const Pk p0 = pk[j];
-      const Pk p1 = pk[j + Q];
-      pair_one<T, MODE_FUSED, 1, true>(p0, j, eps2, I, A);
-      pair_one<T, MODE_FUSED, 1, true>(p1, j + Q, eps2, I, A);
+  if constexpr (DIRECT) {
+    if (q < a.Ns) {
+      const Pk p = pk[q];
+      PairAcc<T, 1> A;
+      A.zero();
+      pair_one<T, MODE_FUSED, 1, true>(p, q, eps2, I, A);
+      acc_flush(A, acc);
     }
-    if (j < jend) {
-      pair_one<T, MODE_FUSED, 1, true>(pk[j], j, eps2, I, A);
-      j += Q;
-    }
-    acc_flush(A, acc);
-  }
-}
-
-// The pending update: the massive object's acceleration at stage sa.pstage
-// from that stage's rows (as k_bh_final), then its Runge-Kutta bookkeeping (as
-// rk4_update) on the state in bi.  Every thread ends with the result in out
-// and the state of this stage's evaluation in own; workgroup 0 stores out (and
-// the new step-start state after stage 3).
-__device__ __forceinline__ void stage_bh_update(const StageArgs& sa, const double (&prows)[7],
-                                                const double (&phrows)[3], const double (&bi)[18],
-                                                double (&out)[18], BhStage& own) {
-  const EpiArgs& a = sa.e;
-  double A0[3], V0, P[3], r[3];
-  bh_quantities<double>(a, prows, A0, V0, P);
-  rows_sum<3>(phrows, r);
-  const int ps = sa.pstage;
-  bool finite = true;
-#pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    const double atc = A0[c] + a.lam * r[c];
-    finite = finite && isfinite(atc);
-    const double X = bi[c], V = bi[3 + c], vs = bi[9 + c], KX = bi[12 + c], KV = bi[15 + c];
-    const double xn = rk4_next(ps, a.dt, X, KX, vs);
-    const double vn = rk4_next(ps, a.dt, V, KV, atc);
-    if (ps < 3) {
-      out[c] = X;
-      out[3 + c] = V;
-      out[12 + c] = ps == 0 ? vs : KX + 2.0 * vs;
-      out[15 + c] = ps == 0 ? atc : KV + 2.0 * atc;
-    } else {
-      out[c] = xn;
-      out[3 + c] = vn;
-      out[12 + c] = 0.0;
-      out[15 + c] = 0.0;
-    }
-    out[6 + c] = xn;
-    out[9 + c] = vn;
-    own.x0[c] = xn;
-    own.X[c] = out[c];
-    own.KX[c] = out[12 + c];
-    own.v[c] = vn;
-  }
-  if (blockIdx.x == 0) {
-    const int t = threadIdx.x;
-    if (t == 0 && !finite) atomicOr(a.status, 1);
-#pragma unroll
-    for (int c = 0; c < 18; ++c)
-      if (t == c) sa.bhs_out[c] = out[c];
-    if (ps == 3) {
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        if (t == 32 + c) uniform_ptr(a.X)[c] = out[c];
-        if (t == 40 + c) uniform_ptr(a.V)[c] = out[3 + c];
+  } else {
+    const Pk* lp = reinterpret_cast<const Pk*>(tile);
+    for (int j0 = 0; j0 < a.Ns; j0 += kStageTile) {
+      const int n = min(a.Ns - j0, kStageTile);
+      if (j0 > 0) __syncthreads();  // the tile before is no longer read
+      const int words = n * (int)(sizeof(Pk) / 16);
+      const char* src = reinterpret_cast<const char*>(pk + j0);
+      for (int w = wave * 64; w < words; w += 64 * kStageWaves) {
+        // lane l: word w + l (past the end: the last word again) to tile + 16 (w + l)
+        __builtin_amdgcn_global_load_lds(
+            (const __attribute__((address_space(1))) void*)(src +
+                                                            16 * (size_t)min(w + lane, words - 1)),
+            (__attribute__((address_space(3))) void*)(tile + 16 * w), 16, 0, 0);
       }
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      __syncthreads();
+      PairAcc<T, 1> A;
+      A.zero();
+      int j = q;
+      for (; j + Q < n; j += 2 * Q) {
+        const Pk p0 = lp[j];
+        const Pk p1 = lp[j + Q];
+        pair_one<T, MODE_FUSED, 1, true>(p0, j0 + j, eps2, I, A);
+        pair_one<T, MODE_FUSED, 1, true>(p1, j0 + j + Q, eps2, I, A);
+      }
+      if (j < n) pair_one<T, MODE_FUSED, 1, true>(lp[j], j0 + j, eps2, I, A);
+      acc_flush(A, acc);
     }
   }
-}
-
-template <typename T, int NS>
-__global__ __launch_bounds__(kBlock) void k_stage(StageArgs sa) {
-  static_assert(kBlock == 256 && 64 % NS == 0 && NS * kNF <= kBlock, "stars per workgroup");
-  __shared__ double red[kNF * 4 * NS];
-  __shared__ double lds[10 * kBlock];
-  __shared__ double fsum[kNF * NS];
-  const EpiArgs& a = sa.e;
-  const int t = threadIdx.x;
-  const bool pend = sa.mode != kStageFirst;
-  const bool eval = sa.mode != kStageFinal;
-  // reads first: the pending update's rows and state, this stage's rows
-  double prows[7], phrows[3], rows[7], bi[18];
-  if (pend) {
-    rows_load<7>(sa.prow, a.nbpro, 8, prows);
-    rows_load<3>(sa.phrow, a.nbpro, 4, phrows);
+  double x[12], r[fold_regs<NS>()];
+  int f[fold_regs<NS>()];
 #pragma unroll
-    for (int c = 0; c < 18; ++c) bi[c] = sa.bhs_in[c];
-  } else {
+  for (int c = 0; c < 12; ++c) x[c] = c < kNF ? acc[c < kNF ? c : 0][0] : 0.0;
+  fold12<NS>(x, r, f);
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      bi[c] = bi[6 + c] = a.X[c];
-      bi[3 + c] = bi[9 + c] = a.V[c];
-      bi[12 + c] = bi[15 + c] = 0.0;
-    }
-  }
-  if (eval) {
-    rows_load<7>(a.bpart, a.nbpro, 8, rows);
-    double acc[kNF][1];
-    stage_sweep<T, NS>(sa, acc);
-    // a star's lanes within a wavefront are NS apart: an xor butterfly over
-    // distances NS ... 32 sums them (the same bits in each), and lane sl < NS
-    // of wavefront w parks star sl's partial
-#pragma unroll
-    for (int m = NS; m < 64; m <<= 1) {
-#pragma unroll
-      for (int f = 0; f < kNF; ++f) acc[f][0] += __shfl_xor(acc[f][0], m, 64);
-    }
-    if ((t & 63) < NS) {
-#pragma unroll
-      for (int f = 0; f < kNF; ++f) red[(f * 4 + (t >> 6)) * NS + (t & 63)] = acc[f][0];
-    }
-  }
-  BhStage own;
-  if (pend) {
-    double out[18];
-    stage_bh_update(sa, prows, phrows, bi, out, own);
-  } else {
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      own.x0[c] = own.X[c] = bi[c];
-      own.KX[c] = 0.0;
-      own.v[c] = bi[3 + c];
-    }
-    if (blockIdx.x == 0) {
-#pragma unroll
-      for (int c = 0; c < 18; ++c)
-        if (t == c) sa.bhs_out[c] = bi[c];
-    }
-  }
-  if (!eval) return;
+  for (int c = 0; c < fold_regs<NS>(); ++c)
+    if (f[c] >= 0 && f[c] < kNF) red[(f[c] * kStageWaves + wave) * NS + lane % NS] = r[c];
   __syncthreads();
-  if (t < NS * kNF) {  // star sl, field f: the four wavefronts' partials in order
-    const int sl = t % NS, f = t / NS;
-    fsum[f * NS + sl] = ((red[(f * 4) * NS + sl] + red[(f * 4 + 1) * NS + sl]) +
-                         red[(f * 4 + 2) * NS + sl]) + red[(f * 4 + 3) * NS + sl];
-  }
-  __syncthreads();
-  epilogue_rows<double, T, NS, true>(a, blockIdx.x, lds, fsum, rows, own);
 }
 
 // A call's first packets, u/b rows and block rows in the stage kernel's
 // layout (a block row per NS stars, reduced as its epilogue reduces them, so
 // that a run resumed from a saved state repeats the continuous run bit for bit).
 template <typename T, int NS>
-__global__ __launch_bounds__(kBlock) void k_stage_head(EpiArgs a) {
+__global__ __launch_bounds__(kBlock) void k_stage_head(EpiArgs a, double* bhs) {
   const int t = threadIdx.x, k = blockIdx.x * NS + t;
   double v[7] = {0, 0, 0, 0, 0, 0, 0};
   if (t < NS && k < a.Ns) {
@@ -1657,12 +1889,16 @@ __global__ __launch_bounds__(kBlock) void k_stage_head(EpiArgs a) {
                           a.ub_next, k, v);
   }
   if (t < 64) {  // the stars are in wavefront 0 (as in the stage's epilogue)
-    wave_allsum<7>(v);
-    if (t < 8) a.bpart_next[(size_t)blockIdx.x * 8 + t] = t < 7 ? pick(v, t) : 0.0;
+    star_sum<NS, 7>(v);
+    if (t == 0) {
+#pragma unroll
+      for (int c = 0; c < 7; ++c) a.bpart_next[(size_t)c * gridDim.x + blockIdx.x] = v[c];
+    }
   }
-  if (blockIdx.x == 0 && t == 0) {
+  if (blockIdx.x == 0) {  // the massive object's state before the first stage
+    if (t < kBhState) bhs[t] = t < 12 ? (t / 3 % 2 ? a.vel : a.pos)[t % 3] : 0.0;
     const double M = a.mass[0];
-    if (!(M > 0.0) || !isfinite(M)) atomicOr(a.status, 2);
+    if (t == 0 && (!(M > 0.0) || !isfinite(M))) atomicOr(a.status, 2);
   }
 }
 
@@ -2300,17 +2536,15 @@ __global__ __launch_bounds__(kBlock) void k_pair_batched(BatchArgs b) {
 }
 
 __global__ __launch_bounds__(kBlock) void k_epilogue_batched(BatchArgs b) {
-  __shared__ double lds[7 * kBlock];
   __shared__ double fsum[kNF * kEpiStars];
   const int r = batch_rank(b.pre, b.n_sys, blockIdx.x);
   const SysDev S = b.sys[b.order[r]];
-  epilogue_block<double>(batch_epi_args(b, S), blockIdx.x - b.pre[r], lds, fsum);
+  epilogue_block<double>(batch_epi_args(b, S), blockIdx.x - b.pre[r], fsum);
 }
 
 __global__ __launch_bounds__(kBlock) void k_bh_final_batched(BatchArgs b) {
-  __shared__ double lds[7 * kBlock];
   const SysDev S = b.sys[b.order[blockIdx.x]];
-  bh_final_block<double>(batch_epi_args(b, S), lds);
+  bh_final_block<double>(batch_epi_args(b, S));
 }
 
 }  // namespace pn

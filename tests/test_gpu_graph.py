@@ -41,7 +41,7 @@ def _advance(pn, kind, prec, P, V, M, n, flags=0):
 
 
 # one-launch stages (N = 100), chained stages, the Hermite steps, an ensemble
-CASES = [("step", 100, 0), ("step", 100, 1), ("step", 700, 0), ("step", 700, 1),
+CASES = [("step", 100, 0), ("step", 100, 1), ("step", 2200, 0), ("step", 2200, 1),
          ("hermite", 150, 0), ("ensemble", 300, 0), ("ensemble", 300, 1)]
 
 
