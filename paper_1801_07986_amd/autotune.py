@@ -175,7 +175,7 @@ def tune_batched(log=print, steps=2, reps=2):
     return out
 
 
-STAGE_SIZES = [100, 160, 512, 1024, 2048, 4096]
+STAGE_SIZES = [100, 160, 512, 1024, 2048, 2500, 3000, 4096, 6000]
 STAGE_NS = (2, 4, 8, 16)
 
 
@@ -206,6 +206,8 @@ def tune_stage(log=print):
                     f"{ms:.4f} ms/step")
                 if ms < best[0]:
                     best = (ms, ns)
+            if best[0] > 0.97 * chain:  # within the runs' spread
+                best = (chain, 0)
             rows.append(dict(N=N, precision=prec_name, ns=best[1], step_ms=best[0],
                              chain_step_ms=chain))
             log(f"[autotune] N={N} {prec_name}: chained {chain:.4f} ms/step, best "
@@ -223,7 +225,7 @@ def tune_stage(log=print):
             hi = int(math.sqrt(r["N"] * (rs[k + 1]["N"] if k + 1 < len(rs) else 2 * r["N"])))
             # a workgroup fills a CU's wavefront slots: beyond one per CU the
             # rest wait for a second pass (FP64, 4 stars per workgroup: N = 1025
-            # 37.1 us per step, 1100 69.4)
+            # 32.7 us per step, 1100 62.7)
             hi = max(min(hi, 256 * r["ns"] + 1), r["N"])
             entries.append(dict(precision=prec, n_min=lo, n_max=hi, ns=r["ns"], measured_N=r["N"],
                                 step_ms=round(r["step_ms"], 5),

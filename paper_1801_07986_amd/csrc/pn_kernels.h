@@ -1519,16 +1519,20 @@ __global__ __launch_bounds__(pair_threads<WS>()) void k_pair_bh(PairArgs a, EpiA
 // launch wrote (the same sums in the same order, so the same bits everywhere);
 // workgroup 0 stores it.  That wavefront then runs the stars' epilogue.  Rows
 // lie across columns, so that its loads are contiguous.  Where every lane has
-// one j at most (DIRECT) it loads that packet itself; else the packets pass
-// through LDS, kStageTile at a time, copied by direct loads that are all in
-// flight at once.
+// one j at most (DIRECT) it loads that packet itself; else each wavefront has a
+// run of j and copies its packets to LDS itself, 64 at a time and the next 64
+// meanwhile, so that no wavefront waits for another before the sums are due.
+// (One tile for all, behind a barrier, waited for the massive object's loads,
+// too: 37.0 us per step instead of 32.7 at N = 1024.)
 // A stage of 100 stars (2 per workgroup), in us from its first instruction:
-// the massive object's loads back at 1.6, its sums 1.9, its update 2.5 (the
-// sweep done at 1.5), the epilogue 4.9, its rows 5.1, the next launch 6.3.
-// 1024 stars (4 per workgroup): packets in LDS 1.9, swept 5.6, epilogue 9.0.
+// the massive object's loads back at 1.2, its sums 1.5, its update 2.2 (the
+// sweep done at 1.7), the epilogue 4.7, its rows 4.9, the next launch 6.2.
+// 1024 stars (4 per workgroup): update 3.7, swept 4.5 to 5.5, epilogue 7.6.
+// Two stars per lane, four packets at a time, or the next packet ahead of the
+// present one: no faster.
 // Against two wavefronts' sweep with the epilogue and the update after it, in
-// us per RK4 step: 34.6 -> 21.8 (100 stars), 40.0 -> 26.4 (300), and 50.8
-// (the two-kernel stages) -> 37.0 (1024).
+// us per RK4 step: 34.6 -> 21.5 (100 stars), 40.0 -> 25.5 (300), and against
+// the two-kernel stages 50.3 -> 32.7 (1024), 71.8 -> 56.7 (2048).
 // Every buffer a stage reads is one no workgroup of that stage writes:
 // packets, u/b rows, block rows, massive-object 1PN rows and the massive
 // object's state (X, V, Xs, Vs, KX, KV and its last Newtonian acceleration)
@@ -1539,7 +1543,6 @@ constexpr int kStageFull = 1;   // pending update, sweep and epilogue
 constexpr int kStageFinal = 2;  // the last pending update only (one workgroup)
 constexpr int kStageWaves = 8;  // wavefronts of the sweep
 constexpr int kStageThreads = 64 * (kStageWaves + 1);
-constexpr int kStageTile = 1024;  // packets in LDS
 
 struct StageArgs {
   EpiArgs e;             // this stage's epilogue; e.nbpro workgroups (rows in every row buffer)
@@ -1554,29 +1557,34 @@ struct StageArgs {
 };
 constexpr int kBhState = 21;
 
-// Column sums, this lane's part: rows l, l + 64, ... of K columns of n rows, in
-// order; the loads of several rows are in flight together.
-template <int K>
-__device__ __forceinline__ void cols_load(const double* part, int n, double* v) {
+// Column sums, this lane's part: rows l, l + 64, ... of n, of three columns of
+// p3 and seven of p7, in order; the loads of several rows are in flight together.
+__device__ __forceinline__ void cols_load(const double* p3, const double* p7, int n,
+                                          double (&v)[10]) {
   const int l = threadIdx.x & 63;
+  const auto row = [&](double (&w)[10], int r) {
 #pragma unroll
-  for (int k = 0; k < K; ++k) v[k] = part[(size_t)k * n + min(l, n - 1)];
-  if (l >= n) {
+    for (int k = 0; k < 10; ++k)
+      w[k] = k < 3 ? p3[(size_t)k * n + min(r, n - 1)] : p7[(size_t)(k - 3) * n + min(r, n - 1)];
+  };
+  const auto add = [&](const double (&w)[10], int r) {
 #pragma unroll
-    for (int k = 0; k < K; ++k) v[k] = 0.0;
-  }
-  constexpr int U = 2;
+    for (int k = 0; k < 10; ++k) v[k] += r < n ? w[k] : 0.0;
+  };
+#pragma unroll
+  for (int k = 0; k < 10; ++k) v[k] = 0.0;
+  constexpr int U = 3;
+  double w0[10];
+  row(w0, l);
   for (int r = l + 64; r - l < n; r += U * 64) {
-    double w[U][K];
+    double w[U][10];
 #pragma unroll
-    for (int u = 0; u < U; ++u)
+    for (int u = 0; u < U; ++u) row(w[u], r + 64 * u);
+    if (r - l == 64) add(w0, l);
 #pragma unroll
-      for (int k = 0; k < K; ++k) w[u][k] = part[(size_t)k * n + min(r + 64 * u, n - 1)];
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-      for (int k = 0; k < K; ++k) v[k] += r + 64 * u < n ? w[u][k] : 0.0;
+    for (int u = 0; u < U; ++u) add(w[u], r + 64 * u);
   }
+  if (n <= 64) add(w0, l);
 }
 
 // Two values folded into one register of sums: the lanes with bit M clear end
@@ -1648,6 +1656,14 @@ __device__ __forceinline__ void fold12(const double (&x)[12], double (&r)[fold_r
   }
 }
 
+// Lane l's x, as a scalar.
+__device__ __forceinline__ double lane_value(double x, int l) {
+  const unsigned long long u = __builtin_bit_cast(unsigned long long, x);
+  const unsigned lo = __builtin_amdgcn_readlane((int)(unsigned)u, l);
+  const unsigned hi = __builtin_amdgcn_readlane((int)(unsigned)(u >> 32), l);
+  return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+
 // Ten values summed over a wavefront, as scalars.
 __device__ __forceinline__ void sum10(double (&v)[10]) {
   const double x[12] = {v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7], v[8], v[9], 0.0, 0.0};
@@ -1659,10 +1675,7 @@ __device__ __forceinline__ void sum10(double (&v)[10]) {
   for (int k = 0; k < 10; ++k) {
     // a lane that holds value k: row of 16 by k % 4, then 8 or 4 by k / 4
     const int lane = (k & 1) * 32 + (k >> 1 & 1) * 16 + (k < 4 ? 0 : k < 8 ? 8 : 4);
-    const unsigned long long u = __builtin_bit_cast(unsigned long long, r[0]);
-    const unsigned lo = __builtin_amdgcn_readlane((int)(unsigned)u, lane);
-    const unsigned hi = __builtin_amdgcn_readlane((int)(unsigned)(u >> 32), lane);
-    v[k] = __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+    v[k] = lane_value(r[0], lane);
   }
 }
 
@@ -1726,14 +1739,18 @@ __device__ __forceinline__ EpiStar<double> stage_star_load(const EpiArgs& a, int
   return in;
 }
 
+// Waits until N copies to LDS at most are on their way.
+template <int N>
+__device__ __forceinline__ void wait_vmcnt() {
+  asm volatile("s_waitcnt vmcnt(%0)" ::"i"(N) : "memory");
+}
+
 template <typename T, int NS, bool DIRECT>
 __global__ __launch_bounds__(kStageThreads) void k_stage(StageArgs sa) {
   using Pk = typename PkOf<T>::type;
-  constexpr int Q = 64 * kStageWaves / NS;  // lanes per star
+  constexpr int W = sizeof(Pk) / 16;  // copies of 16 bytes per lane to stage a tile
   static_assert(sizeof(Pk) % 16 == 0, "copied in 16-byte words");
-  static_assert(kStageTile / Q <= kTile || sizeof(T) == 8, "terms per FP32 partial sum");
-  // (64 words more: the last wavefront's copy may run past the tile)
-  __shared__ __align__(16) char tile[DIRECT ? 16 : (kStageTile * sizeof(Pk) + 64 * 16)];
+  __shared__ __align__(16) char tile[DIRECT ? 16 : 2 * kStageWaves * 64 * sizeof(Pk)];
   __shared__ double red[kNF * kStageWaves * NS];
   __shared__ double fsum[kNF * NS];
   const EpiArgs& a = sa.e;
@@ -1752,22 +1769,16 @@ __global__ __launch_bounds__(kStageThreads) void k_stage(StageArgs sa) {
     double v[10], bi[kBhState];  // row sums: 1PN of the pending stage (3), this stage's (7)
     EpiBh<double> B;
     EpiStar<double> in = stage_star_load(a, min(k, a.Ns - 1));
-#pragma unroll
-    for (int c = 0; c < kBhState; ++c) bi[c] = sa.bhs_in[c];
+    const double state = sa.bhs_in[min(lane, kBhState - 1)];
     B.M = a.mass[0];
-    cols_load<3>(sa.phrow, nb, v);  // (read, not used, where nothing is pending)
-    cols_load<7>(a.bpart, nb, v + 3);
+    cols_load(sa.phrow, a.bpart, nb, v);  // (phrow: read, not used, where nothing is pending)
     if (a.stage == 0) {
 #pragma unroll
       for (int c = 0; c < 3; ++c) in.rk[c].KX = in.rk[c].KV = 0.0;
     }
-    if (eval && !DIRECT) {  // the tiles' barriers
-      for (int j0 = 0; j0 < a.Ns; j0 += kStageTile) {
-        if (j0 > 0) __syncthreads();
-        __syncthreads();
-      }
-    }
     sum10(v);
+#pragma unroll
+    for (int c = 0; c < kBhState; ++c) bi[c] = lane_value(state, c);
     const double iM = 1.0 / B.M;
     if (pend) stage_bh_update(sa, v, bi);
 #pragma unroll
@@ -1809,7 +1820,7 @@ __global__ __launch_bounds__(kStageThreads) void k_stage(StageArgs sa) {
 
   if (!eval) return;
   const Pk* __restrict__ pk = static_cast<const Pk*>(sa.pk);
-  const int sl = threadIdx.x % NS, q = threadIdx.x / NS;
+  const int sl = threadIdx.x % NS;
   PairI<T, 1> I;
   I.idx[0] = blockIdx.x * NS + sl;
   {
@@ -1822,46 +1833,60 @@ __global__ __launch_bounds__(kStageThreads) void k_stage(StageArgs sa) {
     I.kz[0] = T(PairScale<T>::k) * (T)p.svz;
   }
   const T eps2 = (T)a.eps2;
+  PairAcc<T, 1> A;
+  A.zero();
   double acc[kNF][1];
 #pragma unroll
   for (int f = 0; f < kNF; ++f) acc[f][0] = 0.0;
   if constexpr (DIRECT) {
-    if (q < a.Ns) {
+    if (const int q = threadIdx.x / NS; q < a.Ns) {
       const Pk p = pk[q];
-      PairAcc<T, 1> A;
-      A.zero();
       pair_one<T, MODE_FUSED, 1, true>(p, q, eps2, I, A);
-      acc_flush(A, acc);
     }
   } else {
-    const Pk* lp = reinterpret_cast<const Pk*>(tile);
-    for (int j0 = 0; j0 < a.Ns; j0 += kStageTile) {
-      const int n = min(a.Ns - j0, kStageTile);
-      if (j0 > 0) __syncthreads();  // the tile before is no longer read
-      const int words = n * (int)(sizeof(Pk) / 16);
-      const char* src = reinterpret_cast<const char*>(pk + j0);
-      for (int w = wave * 64; w < words; w += 64 * kStageWaves) {
-        // lane l: word w + l (past the end: the last word again) to tile + 16 (w + l)
+    // this wavefront's j, 64 at a time, the next 64 on their way meanwhile
+    const int per = (a.Ns + kStageWaves - 1) / kStageWaves;
+    const int jb = wave * per, n = min(a.Ns - jb, per);
+    char* const mine = tile + wave * (2 * 64 * sizeof(Pk));
+    const char* const src = reinterpret_cast<const char*>(pk + jb);
+    const auto stage_tile = [&](int j0) {
+#pragma unroll
+      for (int w = 0; w < W; ++w) {
+        // word 64 w + lane of the tile (past the end: the last word again)
+        const int word = min(j0 * W + 64 * w + lane, n * W - 1);
         __builtin_amdgcn_global_load_lds(
-            (const __attribute__((address_space(1))) void*)(src +
-                                                            16 * (size_t)min(w + lane, words - 1)),
-            (__attribute__((address_space(3))) void*)(tile + 16 * w), 16, 0, 0);
+            (const __attribute__((address_space(1))) void*)(src + 16 * (size_t)word),
+            (__attribute__((address_space(3))) void*)(mine + (j0 & 64) * sizeof(Pk) + 1024 * w),
+            16, 0, 0);
       }
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      __syncthreads();
-      PairAcc<T, 1> A;
-      A.zero();
-      int j = q;
-      for (; j + Q < n; j += 2 * Q) {
+    };
+    if (n > 0) stage_tile(0);
+    if (n > 64) stage_tile(64);
+    for (int j0 = 0; j0 < n; j0 += 64) {
+      if (j0 + 64 < n) wait_vmcnt<W>();
+      else wait_vmcnt<0>();
+      const Pk* lp = reinterpret_cast<const Pk*>(mine + (j0 & 64) * sizeof(Pk));
+      const int m = min(n - j0, 64);
+      constexpr int Q = 64 / NS;  // j at a time
+      int j = lane / NS;
+      for (; j + Q < m; j += 2 * Q) {
         const Pk p0 = lp[j];
         const Pk p1 = lp[j + Q];
-        pair_one<T, MODE_FUSED, 1, true>(p0, j0 + j, eps2, I, A);
-        pair_one<T, MODE_FUSED, 1, true>(p1, j0 + j + Q, eps2, I, A);
+        pair_one<T, MODE_FUSED, 1, true>(p0, jb + j0 + j, eps2, I, A);
+        pair_one<T, MODE_FUSED, 1, true>(p1, jb + j0 + j + Q, eps2, I, A);
       }
-      if (j < n) pair_one<T, MODE_FUSED, 1, true>(lp[j], j0 + j, eps2, I, A);
-      acc_flush(A, acc);
+      if (j < m) pair_one<T, MODE_FUSED, 1, true>(lp[j], jb + j0 + j, eps2, I, A);
+      if constexpr (sizeof(T) < 8) {  // FP32 partial sums: of a few terms
+        acc_flush(A, acc);
+        A.zero();
+      }
+      if (j0 + 128 < n) {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the tile is read
+        stage_tile(j0 + 128);
+      }
     }
   }
+  if constexpr (DIRECT || sizeof(T) == 8) acc_flush(A, acc);
   double x[12], r[fold_regs<NS>()];
   int f[fold_regs<NS>()];
 #pragma unroll
