@@ -594,22 +594,22 @@ int launch_epilogue(const Sys& s, const Ptrs& P, const Shape& sh, const Outs& o,
   const int ne = (Ns + kEpiStars - 1) / kEpiStars;
   const EpiArgs a = epi_args(s, P, sh, o);
   if (o.jerk_next) {
-    hipLaunchKernelGGL(k_epilogue_chain<Dual>, dim3(ne), dim3(kBlock), 0, st, a);
+    hipLaunchKernelGGL(k_epilogue_chain<Dual>, dim3(ne), dim3(epi_threads<double>()), 0, st, a);
   } else if (o.chain >= 0) {
     if (o.precision == PN_MIXED)
-      hipLaunchKernelGGL(k_epilogue_chain<float>, dim3(ne), dim3(kBlock), 0, st, a);
+      hipLaunchKernelGGL(k_epilogue_chain<float>, dim3(ne), dim3(epi_threads<double>()), 0, st, a);
     else
-      hipLaunchKernelGGL(k_epilogue_chain<double>, dim3(ne), dim3(kBlock), 0, st, a);
+      hipLaunchKernelGGL(k_epilogue_chain<double>, dim3(ne), dim3(epi_threads<double>()), 0, st, a);
   } else if (o.dual && o.fp64_bh) {
-    hipLaunchKernelGGL(k_epilogue_dual_bh, dim3(ne + 1), dim3(kBlock), 0, st, a, *o.fp64_bh);
+    hipLaunchKernelGGL(k_epilogue_dual_bh, dim3(ne + 1), dim3(epi_threads<Dual>()), 0, st, a, *o.fp64_bh);
     HIPCK(hipGetLastError());
     hipLaunchKernelGGL(k_bh_final<Dual>, dim3(1), dim3(kBlock), 0, st, a);
   } else if (o.dual) {
-    hipLaunchKernelGGL(k_epilogue<Dual>, dim3(ne), dim3(kBlock), 0, st, a);
+    hipLaunchKernelGGL(k_epilogue<Dual>, dim3(ne), dim3(epi_threads<Dual>()), 0, st, a);
     HIPCK(hipGetLastError());
     hipLaunchKernelGGL(k_bh_final<Dual>, dim3(1), dim3(kBlock), 0, st, a);
   } else {
-    hipLaunchKernelGGL(k_epilogue<double>, dim3(ne), dim3(kBlock), 0, st, a);
+    hipLaunchKernelGGL(k_epilogue<double>, dim3(ne), dim3(epi_threads<double>()), 0, st, a);
     HIPCK(hipGetLastError());
     hipLaunchKernelGGL(k_bh_final<double>, dim3(1), dim3(kBlock), 0, st, a);
   }
@@ -1211,7 +1211,7 @@ int enqueue_batched_step(const BatchPlan& P, char* base, const double* mass, dou
     }
     HIPCK(hipGetLastError());
     b.pre = pre_epi;
-    hipLaunchKernelGGL(k_epilogue_batched, dim3(P.pre_epi[n_sys]), dim3(kBlock), 0, st, b);
+    hipLaunchKernelGGL(k_epilogue_batched, dim3(P.pre_epi[n_sys]), dim3(epi_threads<double>()), 0, st, b);
     HIPCK(hipGetLastError());
     hipLaunchKernelGGL(k_bh_final_batched, dim3(n_sys), dim3(kBlock), 0, st, b);
     HIPCK(hipGetLastError());

@@ -343,6 +343,117 @@ __device__ __forceinline__ double pick(const double (&v)[K], int col) {
 // and j packets keep coming through scalar loads).
 __device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
 
+// Two values folded into one register of sums: the lanes with bit M clear end
+// with x[i] + x[i ^ M], those with it set with the same sum of y (M = 32, 16: by
+// a swap of halves or rows; 8, 4: by DPP moves within rows, written to the banks
+// of four lanes that lack the value).  Reducing K values over a wavefront this
+// way takes about as many additions as there are values, where summing each of
+// them in all lanes takes one per value and level.
+template <int M>
+__device__ __forceinline__ double fold(double x, double y) {
+  const unsigned long long ux = __builtin_bit_cast(unsigned long long, x);
+  const unsigned long long uy = __builtin_bit_cast(unsigned long long, y);
+  const unsigned xl = (unsigned)ux, xh = (unsigned)(ux >> 32);
+  const unsigned yl = (unsigned)uy, yh = (unsigned)(uy >> 32);
+  unsigned al, ah, bl, bh;
+  if constexpr (M == 32) {
+    const auto l = __builtin_amdgcn_permlane32_swap(xl, yl, false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap(xh, yh, false, false);
+    al = l[0], bl = l[1], ah = h[0], bh = h[1];
+  } else if constexpr (M == 16) {
+    const auto l = __builtin_amdgcn_permlane16_swap(xl, yl, false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap(xh, yh, false, false);
+    al = l[0], bl = l[1], ah = h[0], bh = h[1];
+  } else {
+    // a: x, with y shifted up by M in the lanes with bit M set; b: y, with x
+    // shifted down in the others
+    constexpr int set = M == 8 ? 0xC : 0xA, clear = M == 8 ? 0x3 : 0x5;
+    al = __builtin_amdgcn_update_dpp((int)xl, (int)yl, 0x110 + M, 0xF, set, false);
+    ah = __builtin_amdgcn_update_dpp((int)xh, (int)yh, 0x110 + M, 0xF, set, false);
+    bl = __builtin_amdgcn_update_dpp((int)yl, (int)xl, 0x100 + M, 0xF, clear, false);
+    bh = __builtin_amdgcn_update_dpp((int)yh, (int)xh, 0x100 + M, 0xF, clear, false);
+  }
+  return __builtin_bit_cast(double, ((unsigned long long)ah << 32) | al) +
+         __builtin_bit_cast(double, ((unsigned long long)bh << 32) | bl);
+}
+
+// Twelve values reduced over the lanes that are NS apart: the lane's results
+// r[0 .. fold_regs - 1] are the sums of the values f[0 ..] of residue lane % NS
+// (f = -1: a copy of another lane's).
+template <int NS>
+constexpr int fold_regs() { return NS >= 16 ? 3 : NS == 8 ? 2 : 1; }
+template <int NS>
+__device__ __forceinline__ void fold12(const double (&x)[12], double (&r)[fold_regs<NS>()],
+                                       int (&f)[fold_regs<NS>()]) {
+  const int lane = threadIdx.x & 63;
+  const int row = (lane >> 4 & 1) * 2 + (lane >> 5);  // which of four values a row of 16 holds
+  double z[3];
+#pragma unroll
+  for (int i = 0; i < 3; ++i)
+    z[i] = fold<16>(fold<32>(x[4 * i], x[4 * i + 1]), fold<32>(x[4 * i + 2], x[4 * i + 3]));
+  if constexpr (NS >= 16) {
+#pragma unroll
+    for (int i = 0; i < 3; ++i) r[i] = z[i], f[i] = 4 * i + row;
+  } else {
+    const int b8 = lane >> 3 & 1;
+    const double u = fold<8>(z[0], z[1]), w = z[2] + dpp_d<0x128>(z[2]);
+    if constexpr (NS == 8) {
+      r[0] = u, f[0] = 4 * b8 + row;
+      r[1] = w, f[1] = b8 ? -1 : 8 + row;
+    } else {
+      const int b4 = lane >> 2 & 1;
+      r[0] = fold<4>(u, w);
+      f[0] = !b4 ? 4 * b8 + row : b8 ? -1 : 8 + row;
+      if constexpr (NS == 2) {
+        r[0] += dpp_d<0x4E>(r[0]);  // lane ^ 2
+        if (lane & 2) f[0] = -1;
+      }
+    }
+  }
+}
+
+// Lane l's x, as a scalar.
+__device__ __forceinline__ double lane_value(double x, int l) {
+  const unsigned long long u = __builtin_bit_cast(unsigned long long, x);
+  const unsigned lo = __builtin_amdgcn_readlane((int)(unsigned)u, l);
+  const unsigned hi = __builtin_amdgcn_readlane((int)(unsigned)(u >> 32), l);
+  return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+
+// Ten values summed over a wavefront, as scalars.
+__device__ __forceinline__ void sum10(double (&v)[10]) {
+  const double x[12] = {v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7], v[8], v[9], 0.0, 0.0};
+  double r[1];
+  int f[1];
+  fold12<2>(x, r, f);
+  r[0] += dpp_d<0xB1>(r[0]);  // lane ^ 1: every lane now holds the whole sum of its value
+#pragma unroll
+  for (int k = 0; k < 10; ++k) {
+    // a lane that holds value k: row of 16 by k % 4, then 8 or 4 by k / 4
+    const int lane = (k & 1) * 32 + (k >> 1 & 1) * 16 + (k < 4 ? 0 : k < 8 ? 8 : 4);
+    v[k] = lane_value(r[0], lane);
+  }
+}
+
+// Sums over the wavefront, in every lane, ten at a time by folds: fewer
+// instructions than wave_allsum (ten values of a wavefront alone: 0.3 us
+// instead of 0.7), and the same additions for every value, so that the block
+// sums of a chained epilogue, an epilogue alone and a prologue agree bit for
+// bit.
+template <int K>
+__device__ __forceinline__ void wave_sum(double (&v)[K]) {
+#pragma unroll
+  for (int k0 = 0; k0 < K; k0 += 10) {
+    double x[10];
+#pragma unroll
+    for (int k = 0; k < 10; ++k) x[k] = k0 + k < K ? v[k0 + k < K ? k0 + k : 0] : 0.0;
+    sum10(x);
+#pragma unroll
+    for (int k = 0; k < 10; ++k)
+      if (k0 + k < K) v[k0 + k < K ? k0 + k : 0] = x[k];
+  }
+}
+
 // Sum of `rows` partial rows of width `stride` (first K columns), fixed order:
 // lane l of every wavefront sums rows l, l+64, ..., then wave_allsum.  Every
 // thread of every workgroup ends with the same bits, without a barrier.
@@ -361,16 +472,25 @@ __device__ __forceinline__ void rows_load(const double* part, int rows, int stri
 #pragma unroll
     for (int k = 0; k < K; ++k) v[k] = part[(size_t)l * stride + k];
   }
-  for (int r = l + 64; r < rows; r += 64) {
+  constexpr int U = K <= 8 ? 3 : 1;  // further rows in flight together
+  for (int r = l + 64; r - l < rows; r += U * 64) {
+    double w[U][K];
 #pragma unroll
-    for (int k = 0; k < K; ++k) v[k] += part[(size_t)r * stride + k];
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int k = 0; k < K; ++k)
+        w[u][k] = part[(size_t)min(r + 64 * u, rows - 1) * stride + k];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int k = 0; k < K; ++k) v[k] += r + 64 * u < rows ? w[u][k] : 0.0;
   }
 }
 template <int K>
 __device__ __forceinline__ void rows_sum(const double (&v)[K], double (&out)[K]) {
 #pragma unroll
   for (int k = 0; k < K; ++k) out[k] = v[k];
-  wave_allsum<K>(out);
+  wave_sum<K>(out);
 }
 template <int K>
 __device__ __forceinline__ void reduce_rows(const double* part, int rows, int stride,
@@ -469,12 +589,12 @@ __device__ __forceinline__ void prologue_block(const ProArgs& a, int blk) {
     }
     star_terms<T, S>(x0, xs, vs, a.mass[s], a.G, a.G * a.mass[0], a.eps2, a.pk, a.ub, k, v);
   }
-  // a block row per wavefront (64 stars), summed by wave_allsum and written
+  // a block row per wavefront (64 stars), summed by wave_sum and written
   // from the wavefront's own registers
   double flat[7 * W];
 #pragma unroll
   for (int q = 0; q < 7; ++q) put(flat, q, 7, v[q]);
-  wave_allsum<7 * W>(flat);
+  wave_sum<7 * W>(flat);
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
   if (l < 8 * W) {
     // row layout: value columns 0..7, derivative columns 8..15 (Dual)
@@ -1037,7 +1157,17 @@ __device__ __forceinline__ void bh_quantities(const EpiArgs& a,
   }
 }
 
-constexpr int kEpiStars = 64;  // stars per epilogue workgroup (4 threads per star reduce the splits)
+constexpr int kEpiStars = 64;  // stars per epilogue workgroup
+// Split ranges that an epilogue workgroup sums side by side (four wavefronts
+// each), the wavefronts that do so, and all its threads: one wavefront more
+// runs the epilogue.  (The dual epilogue's needs more than 168 registers per
+// lane, of which nine wavefronts fit a CU.)
+template <typename S>
+constexpr int epi_ranges() { return IsDual<S>::value ? 1 : 2; }
+template <typename S>
+constexpr int epi_threads() { return 64 * (4 * epi_ranges<S>() + 1); }
+template <typename S>
+constexpr int epi_fsum() { return kNF * Width<S>::n * kEpiStars * epi_ranges<S>(); }
 
 __device__ __forceinline__ bool epi_field_used(int f, const EpiArgs& a) {
   f %= kNF;
@@ -1136,6 +1266,13 @@ __device__ __forceinline__ EpiGeo<S> epi_geo(const EpiArgs& a, const EpiStar<S>&
   g.g7s = 3.5 * gm_s * g.rinv0;
   return g;
 }
+// Holds them before a wait: the compiler would move them behind it.
+__device__ __forceinline__ void geo_hold(EpiGeo<double>& g) {
+  asm volatile("" : "+v"(g.vi2), "+v"(g.kk), "+v"(g.vw), "+v"(g.dA), "+v"(g.n4v), "+v"(g.nw),
+               "+v"(g.g7), "+v"(g.n0[0]), "+v"(g.n0[1]), "+v"(g.n0[2]));
+  asm volatile("" : "+v"(g.ks), "+v"(g.nvs), "+v"(g.nws), "+v"(g.g7s));
+}
+__device__ __forceinline__ void geo_hold(EpiGeo<Dual>&) {}
 
 // Star k's epilogue from its pair sums: outputs, stage update and next
 // packet.  bh: its term of the massive object's 1PN sum; pro: its block-sum
@@ -1279,7 +1416,7 @@ __device__ __forceinline__ void epi_rows(const EpiArgs& a, int blk, const S (&bh
       }
     }
   } else {
-    wave_allsum<NB>(bhs);
+    wave_sum<NB>(bhs);
     if (l < 4 * W) {
       // row layout: values in columns 0..2, derivatives in 4..6 (Dual)
       const int q = l & 3, h = l >> 2;
@@ -1298,19 +1435,75 @@ __device__ __forceinline__ void epi_rows(const EpiArgs& a, int blk, const S (&bh
 }
 
 // The epilogue of kEpiStars stars (blk * kEpiStars ...) from the splits'
-// partial sums; fsum: kNF W kEpiStars doubles of LDS.
+// partial sums; fsum: epi_fsum doubles of LDS.  It is a chain of latencies, so
+// the wavefronts that sum the splits leave everything else to one more, which
+// meanwhile loads the stars' own inputs and the prologue rows and prepares
+// what does not wait for the sums.  1500 stars, in us from its first
+// instruction: loads back 1.0, massive object 1.5, split sums 1.7, terms
+// prepared 1.9, barrier 2.4, star 4.0, block sums 4.5, stored 4.6.  With all
+// four wavefronts doing everything in turn, 8 splits at a time, an RK4 step
+// took 56.1 us instead of 50.9 at N = 1200, 142.0 instead of 137.3 at 4097
+// and 633 instead of 627 at 10001 (FP64).
 template <typename S, typename PkT = void>
 __device__ __forceinline__ void epilogue_block(const EpiArgs& a, int blk, double* fsum) {
   constexpr bool DUAL = IsDual<S>::value;
   constexpr int W = DUAL ? 2 : 1;
   constexpr int NFO = kNF * W;
-  static_assert(kEpiStars == 64, "the stars of a workgroup are in its first wavefront");
-  // Every global read of the workgroup is requested before the first wait:
-  // the prologue rows, the pair partials, the star's own inputs and
-  // Runge-Kutta state, the massive object's state.  (At small N this kernel is
-  // a chain of memory latencies; issued in order, they added up.)
-  double rows[bh_cols<S>()];
-  rows_load<bh_cols<S>()>(a.bpart, a.nbpro, DUAL ? 16 : 8, rows);
+  constexpr int R = epi_ranges<S>();
+  static_assert(kEpiStars == 64, "a star per lane");
+  const int wave = wave_id(), l = threadIdx.x & 63;
+  const int k = blk * kEpiStars + l;
+
+  if (wave < 4 * R) {
+    // split reduction: wavefront (h, g) sums fields g, g+4, g+8, ... over the
+    // splits of range h, in split order; the loads of up to 8 (dual: 4) splits
+    // of all its fields are issued together, then added in order
+    constexpr int FPT = (NFO + 3) / 4;   // fields per thread
+    constexpr int BATCH = DUAL ? 4 : 8;  // splits per batch of loads
+    const int g = wave & 3, h = wave >> 2;
+    const int per = (a.nsplit + R - 1) / R;
+    const int s0 = h * per, ns = min(a.nsplit - s0, per);
+    if (k < a.Ns) {
+      const size_t plane = (size_t)a.Ns;
+      const size_t sstride = (size_t)NFO * plane;
+      double sum[FPT];
+      bool use[FPT];
+#pragma unroll
+      for (int fi = 0; fi < FPT; ++fi) {
+        const int f = g + 4 * fi;
+        sum[fi] = 0.0;
+        use[fi] = f < NFO && epi_field_used(f, a);
+      }
+      const double* src = a.part + (size_t)g * plane + (size_t)s0 * sstride + k;
+      for (int sp = 0; sp < ns; sp += BATCH) {
+        double v[FPT][BATCH];
+#pragma unroll
+        for (int fi = 0; fi < FPT; ++fi)
+#pragma unroll
+          for (int q = 0; q < BATCH; ++q)
+            v[fi][q] = (use[fi] && sp + q < ns)
+                           ? src[(size_t)4 * fi * plane + (size_t)(sp + q) * sstride]
+                           : 0.0;
+#pragma unroll
+        for (int fi = 0; fi < FPT; ++fi)
+#pragma unroll
+          for (int q = 0; q < BATCH; ++q)
+            if (sp + q < ns) sum[fi] += v[fi][q];
+      }
+#pragma unroll
+      for (int fi = 0; fi < FPT; ++fi)
+        if (g + 4 * fi < NFO) fsum[(h * NFO + g + 4 * fi) * kEpiStars + l] = sum[fi];
+    }
+    __syncthreads();
+    return;
+  }
+
+  // the massive object and the stars' epilogue: every global read is requested
+  // before the first wait
+  __builtin_amdgcn_s_setprio(3);
+  const bool star = k < a.Ns;
+  EpiStar<S> in;
+  if (star) in = epi_star_load<S>(a, k);
   EpiBh<S> B;
   B.M = a.mass[0];
   for (int c = 0; c < 3; ++c) B.x0[c] = ld<S>(a.pos, a.pos_d, c);
@@ -1325,98 +1518,43 @@ __device__ __forceinline__ void epilogue_block(const EpiArgs& a, int blk, double
       }
     }
   }
-  const int k = blk * kEpiStars + threadIdx.x;
-  const bool star = threadIdx.x < kEpiStars && k < a.Ns;
-  EpiStar<S> in;
-  if (star) in = epi_star_load<S>(a, k);
-
-  // split reduction: thread (g, l) sums fields g, g+4, g+8, ... of star l, in
-  // split order; the loads of up to 8 (dual: 4) splits of all its fields are
-  // issued together, then added in order
-  {
-    constexpr int FPT = (NFO + 3) / 4;      // fields per thread
-    constexpr int BATCH = DUAL ? 4 : 8;     // splits per batch of loads
-    const int g = threadIdx.x >> 6, l = threadIdx.x & 63;
-    const int kk = blk * kEpiStars + l;
-    if (kk < a.Ns) {
-      const size_t plane = (size_t)a.Ns;
-      const size_t sstride = (size_t)NFO * plane;
-      double sum[FPT];
-      bool use[FPT];
-#pragma unroll
-      for (int fi = 0; fi < FPT; ++fi) {
-        const int f = g + 4 * fi;
-        sum[fi] = 0.0;
-        use[fi] = f < NFO && epi_field_used(f, a);
-      }
-      const double* src = a.part + (size_t)g * plane + kk;
-      int sp = 0;
-      for (; sp + BATCH <= a.nsplit; sp += BATCH) {
-        double v[FPT][BATCH];
-#pragma unroll
-        for (int fi = 0; fi < FPT; ++fi)
-#pragma unroll
-          for (int q = 0; q < BATCH; ++q)
-            v[fi][q] = use[fi] ? src[(size_t)4 * fi * plane + (size_t)(sp + q) * sstride] : 0.0;
-#pragma unroll
-        for (int fi = 0; fi < FPT; ++fi)
-#pragma unroll
-          for (int q = 0; q < BATCH; ++q) sum[fi] += v[fi][q];
-      }
-      if (sp < a.nsplit) {  // the remaining splits, also in one batch
-        double v[FPT][BATCH];
-#pragma unroll
-        for (int fi = 0; fi < FPT; ++fi)
-#pragma unroll
-          for (int q = 0; q < BATCH; ++q)
-            v[fi][q] = (use[fi] && sp + q < a.nsplit)
-                           ? src[(size_t)4 * fi * plane + (size_t)(sp + q) * sstride]
-                           : 0.0;
-#pragma unroll
-        for (int fi = 0; fi < FPT; ++fi)
-#pragma unroll
-          for (int q = 0; q < BATCH; ++q)
-            if (sp + q < a.nsplit) sum[fi] += v[fi][q];
-      }
-#pragma unroll
-      for (int fi = 0; fi < FPT; ++fi)
-        if (g + 4 * fi < NFO) fsum[(g + 4 * fi) * kEpiStars + l] = sum[fi];
-    }
-  }
-  __syncthreads();  // fsum complete
+  double rows[bh_cols<S>()];
+  rows_load<bh_cols<S>()>(a.bpart, a.nbpro, DUAL ? 16 : 8, rows);
   S P[3];
   bh_quantities<S>(a, rows, B.A0, B.V0, P);
   const double iM = 1.0 / B.M;
   for (int c = 0; c < 3; ++c) B.w[c] = -(P[c] * iM);
+  EpiGeo<S> geo = epi_geo<S>(a, in, B);
+  geo_hold(geo);
+  __syncthreads();  // fsum complete
 
   S bh[3] = {0.0, 0.0, 0.0};
   double pro[epi_next_terms<PkT>()];
 #pragma unroll
   for (int q = 0; q < epi_next_terms<PkT>(); ++q) pro[q] = 0.0;
   if (star) {
-    const int t = threadIdx.x;
     S sum[kNF];
 #pragma unroll
     for (int f = 0; f < kNF; ++f) {
-      if constexpr (DUAL) sum[f] = S(fsum[f * kEpiStars + t], fsum[(kNF + f) * kEpiStars + t]);
-      else sum[f] = fsum[f * kEpiStars + t];
+      if constexpr (DUAL) sum[f] = S(fsum[f * kEpiStars + l], fsum[(kNF + f) * kEpiStars + l]);
+      else sum[f] = fsum[f * kEpiStars + l] + fsum[(NFO + f) * kEpiStars + l];
     }
-    epi_star<S, PkT>(a, k, in, B, epi_geo<S>(a, in, B), sum, bh, pro);
+    epi_star<S, PkT>(a, k, in, B, geo, sum, bh, pro);
   }
-  if (wave_id() == 0) epi_rows<S, PkT, 0>(a, blk, bh, pro);
+  epi_rows<S, PkT, 0>(a, blk, bh, pro);
 }
 
 template <typename S>
-__global__ __launch_bounds__(kBlock) void k_epilogue(EpiArgs a) {
-  __shared__ double fsum[kNF * Width<S>::n * kEpiStars];
+__global__ __launch_bounds__(epi_threads<S>()) void k_epilogue(EpiArgs a) {
+  __shared__ double fsum[epi_fsum<S>()];
   epilogue_block<S>(a, blockIdx.x, fsum);
 }
 
 // FP64 epilogue that also performs the next sweep's prologue (packets of
 // PkOf<T>; T = Dual: the jerk sweep at this state), saving that kernel.
 template <typename T>
-__global__ __launch_bounds__(kBlock) void k_epilogue_chain(EpiArgs a) {
-  __shared__ double fsum[kNF * kEpiStars];
+__global__ __launch_bounds__(epi_threads<double>()) void k_epilogue_chain(EpiArgs a) {
+  __shared__ double fsum[epi_fsum<double>()];
   epilogue_block<double, T>(a, blockIdx.x, fsum);
 }
 
@@ -1479,8 +1617,8 @@ __global__ __launch_bounds__(kBlock) void k_bh_final(EpiArgs a) {
 // update (k_bh_final<double>'s work) in one extra workgroup: the dual
 // epilogue reads neither the massive object's FP64 acceleration nor the FP64
 // partial rows (its own rows are in separate buffers).
-__global__ __launch_bounds__(kBlock) void k_epilogue_dual_bh(EpiArgs a, EpiArgs e) {
-  __shared__ double fsum[kNF * 2 * kEpiStars];
+__global__ __launch_bounds__(epi_threads<Dual>()) void k_epilogue_dual_bh(EpiArgs a, EpiArgs e) {
+  __shared__ double fsum[epi_fsum<Dual>()];
   if (blockIdx.x == gridDim.x - 1) {
     bh_final_block<double>(e);
     return;
@@ -1585,98 +1723,6 @@ __device__ __forceinline__ void cols_load(const double* p3, const double* p7, in
     for (int u = 0; u < U; ++u) add(w[u], r + 64 * u);
   }
   if (n <= 64) add(w0, l);
-}
-
-// Two values folded into one register of sums: the lanes with bit M clear end
-// with x[i] + x[i ^ M], those with it set with the same sum of y (M = 32, 16: by
-// a swap of halves or rows; 8, 4: by DPP moves within rows, written to the banks
-// of four lanes that lack the value).  Reducing K values over a wavefront this
-// way takes about as many additions as there are values, where summing each of
-// them in all lanes takes one per value and level.
-template <int M>
-__device__ __forceinline__ double fold(double x, double y) {
-  const unsigned long long ux = __builtin_bit_cast(unsigned long long, x);
-  const unsigned long long uy = __builtin_bit_cast(unsigned long long, y);
-  const unsigned xl = (unsigned)ux, xh = (unsigned)(ux >> 32);
-  const unsigned yl = (unsigned)uy, yh = (unsigned)(uy >> 32);
-  unsigned al, ah, bl, bh;
-  if constexpr (M == 32) {
-    const auto l = __builtin_amdgcn_permlane32_swap(xl, yl, false, false);
-    const auto h = __builtin_amdgcn_permlane32_swap(xh, yh, false, false);
-    al = l[0], bl = l[1], ah = h[0], bh = h[1];
-  } else if constexpr (M == 16) {
-    const auto l = __builtin_amdgcn_permlane16_swap(xl, yl, false, false);
-    const auto h = __builtin_amdgcn_permlane16_swap(xh, yh, false, false);
-    al = l[0], bl = l[1], ah = h[0], bh = h[1];
-  } else {
-    // a: x, with y shifted up by M in the lanes with bit M set; b: y, with x
-    // shifted down in the others
-    constexpr int set = M == 8 ? 0xC : 0xA, clear = M == 8 ? 0x3 : 0x5;
-    al = __builtin_amdgcn_update_dpp((int)xl, (int)yl, 0x110 + M, 0xF, set, false);
-    ah = __builtin_amdgcn_update_dpp((int)xh, (int)yh, 0x110 + M, 0xF, set, false);
-    bl = __builtin_amdgcn_update_dpp((int)yl, (int)xl, 0x100 + M, 0xF, clear, false);
-    bh = __builtin_amdgcn_update_dpp((int)yh, (int)xh, 0x100 + M, 0xF, clear, false);
-  }
-  return __builtin_bit_cast(double, ((unsigned long long)ah << 32) | al) +
-         __builtin_bit_cast(double, ((unsigned long long)bh << 32) | bl);
-}
-
-// Twelve values reduced over the lanes that are NS apart: the lane's results
-// r[0 .. fold_regs - 1] are the sums of the values f[0 ..] of residue lane % NS
-// (f = -1: a copy of another lane's).
-template <int NS>
-constexpr int fold_regs() { return NS >= 16 ? 3 : NS == 8 ? 2 : 1; }
-template <int NS>
-__device__ __forceinline__ void fold12(const double (&x)[12], double (&r)[fold_regs<NS>()],
-                                       int (&f)[fold_regs<NS>()]) {
-  const int lane = threadIdx.x & 63;
-  const int row = (lane >> 4 & 1) * 2 + (lane >> 5);  // which of four values a row of 16 holds
-  double z[3];
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-    z[i] = fold<16>(fold<32>(x[4 * i], x[4 * i + 1]), fold<32>(x[4 * i + 2], x[4 * i + 3]));
-  if constexpr (NS >= 16) {
-#pragma unroll
-    for (int i = 0; i < 3; ++i) r[i] = z[i], f[i] = 4 * i + row;
-  } else {
-    const int b8 = lane >> 3 & 1;
-    const double u = fold<8>(z[0], z[1]), w = z[2] + dpp_d<0x128>(z[2]);
-    if constexpr (NS == 8) {
-      r[0] = u, f[0] = 4 * b8 + row;
-      r[1] = w, f[1] = b8 ? -1 : 8 + row;
-    } else {
-      const int b4 = lane >> 2 & 1;
-      r[0] = fold<4>(u, w);
-      f[0] = !b4 ? 4 * b8 + row : b8 ? -1 : 8 + row;
-      if constexpr (NS == 2) {
-        r[0] += dpp_d<0x4E>(r[0]);  // lane ^ 2
-        if (lane & 2) f[0] = -1;
-      }
-    }
-  }
-}
-
-// Lane l's x, as a scalar.
-__device__ __forceinline__ double lane_value(double x, int l) {
-  const unsigned long long u = __builtin_bit_cast(unsigned long long, x);
-  const unsigned lo = __builtin_amdgcn_readlane((int)(unsigned)u, l);
-  const unsigned hi = __builtin_amdgcn_readlane((int)(unsigned)(u >> 32), l);
-  return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
-}
-
-// Ten values summed over a wavefront, as scalars.
-__device__ __forceinline__ void sum10(double (&v)[10]) {
-  const double x[12] = {v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7], v[8], v[9], 0.0, 0.0};
-  double r[1];
-  int f[1];
-  fold12<2>(x, r, f);
-  r[0] += dpp_d<0xB1>(r[0]);  // lane ^ 1: every lane now holds the whole sum of its value
-#pragma unroll
-  for (int k = 0; k < 10; ++k) {
-    // a lane that holds value k: row of 16 by k % 4, then 8 or 4 by k / 4
-    const int lane = (k & 1) * 32 + (k >> 1 & 1) * 16 + (k < 4 ? 0 : k < 8 ? 8 : 4);
-    v[k] = lane_value(r[0], lane);
-  }
 }
 
 // The pending update: the massive object's acceleration at stage sa.pstage (as
@@ -1794,10 +1840,7 @@ __global__ __launch_bounds__(kStageThreads) void k_stage(StageArgs sa) {
     if (blockIdx.x == 0 && lane < kBhState) sa.bhs_out[lane] = pick(bi, lane);
     if (!eval) return;
     EpiGeo<double> g = epi_geo<double>(a, in, B);
-    // held here: otherwise the compiler moves them behind the wait
-    asm volatile("" : "+v"(g.vi2), "+v"(g.kk), "+v"(g.vw), "+v"(g.dA), "+v"(g.n4v), "+v"(g.nw),
-                 "+v"(g.g7), "+v"(g.n0[0]), "+v"(g.n0[1]), "+v"(g.n0[2]));
-    asm volatile("" : "+v"(g.ks), "+v"(g.nvs), "+v"(g.nws), "+v"(g.g7s));
+    geo_hold(g);
     __syncthreads();  // the sweep's sums are in red
     for (int e = lane; e < kNF * NS; e += 64) {  // field e / NS of star e % NS
       const double* r = red + e / NS * kStageWaves * NS + e % NS;
@@ -2560,8 +2603,8 @@ __global__ __launch_bounds__(kBlock) void k_pair_batched(BatchArgs b) {
   pair_block<T, MODE_FUSED, IPT, 4>(a, local % S.iblocks, local / S.iblocks, red);
 }
 
-__global__ __launch_bounds__(kBlock) void k_epilogue_batched(BatchArgs b) {
-  __shared__ double fsum[kNF * kEpiStars];
+__global__ __launch_bounds__(epi_threads<double>()) void k_epilogue_batched(BatchArgs b) {
+  __shared__ double fsum[epi_fsum<double>()];
   const int r = batch_rank(b.pre, b.n_sys, blockIdx.x);
   const SysDev S = b.sys[b.order[r]];
   epilogue_block<double>(batch_epi_args(b, S), blockIdx.x - b.pre[r], fsum);
