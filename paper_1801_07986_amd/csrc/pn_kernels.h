@@ -873,6 +873,27 @@ __device__ __forceinline__ void pair_block(const PairArgs& a, int ib, int sp, do
   const int lane = WS > 1 ? (int)(threadIdx.x & 63) : (int)threadIdx.x;
   const int ilo = ib * IB;
   const int ihi = min(a.Ns, ilo + IB);
+  // j-range of this wavefront
+  int j0 = sp * a.jchunk;
+  int j1 = min(a.Ns, j0 + a.jchunk);
+  if (WS > 1) {
+    const int q = (j1 - j0 + WS - 1) / WS;
+    const int w0 = min(j1, j0 + wave * q);
+    j1 = min(j1, w0 + q);
+    j0 = w0;
+  }
+  // One load per 128 bytes of this wavefront's packets, not used: the epilogue
+  // that wrote them ran on other XCDs, so each line's first scalar load would go
+  // past this XCD's L2, one round trip after the other.  us per RK4 step
+  // without and with it: FP64 N = 1200 50.9, 48.1; 3000 117.7, 108.5; 6000 271,
+  // 260; 10001 627, 612; 16384 the same; mixed 1200 61.5, 49.5; 5000 160, 139;
+  // 10001 471, 431; 30000 3190, 3156; at 2300, 6000 and 8192 mixed about 1 %
+  // slower.  Runs of more than twice the 64 lines have enough to do meanwhile
+  // (one line then; with all of them N = 65536 mixed takes 0.5 % longer).
+  const int run = (j1 - j0) * (int)sizeof(Pk);
+  const unsigned touched = *reinterpret_cast<const unsigned*>(
+      reinterpret_cast<const char*>(pk + j0) +
+      min((run <= 2 * 64 * 128 ? 128 : 0) * (int)(threadIdx.x & 63), max(0, run - 4)));
   PairI<T, IPT> I;
 #pragma unroll
   for (int ii = 0; ii < IPT; ++ii) {
@@ -886,15 +907,6 @@ __device__ __forceinline__ void pair_block(const PairArgs& a, int ib, int sp, do
     I.kx[ii] = T(PairScale<T>::k) * (T)p.svx;
     I.ky[ii] = T(PairScale<T>::k) * (T)p.svy;
     I.kz[ii] = T(PairScale<T>::k) * (T)p.svz;
-  }
-  // j-range of this wavefront
-  int j0 = sp * a.jchunk;
-  int j1 = min(a.Ns, j0 + a.jchunk);
-  if (WS > 1) {
-    const int q = (j1 - j0 + WS - 1) / WS;
-    const int w0 = min(j1, j0 + wave * q);
-    j1 = min(j1, w0 + q);
-    j0 = w0;
   }
   const T eps2 = (T)a.eps2;
 
@@ -918,6 +930,7 @@ __device__ __forceinline__ void pair_block(const PairArgs& a, int ib, int sp, do
     }
   }
 
+  asm volatile("" ::"v"(touched));
   const size_t plane = (size_t)a.Ns;
   double* out = a.part + (size_t)sp * NFO * plane;
   if constexpr (WS == 1) {
@@ -1632,8 +1645,10 @@ __global__ __launch_bounds__(epi_threads<Dual>()) void k_epilogue_dual_bh(EpiArg
 // two are independent and the stage saves a kernel boundary.  Grid: the
 // sweep's (iblocks + 1) x nsplit; column iblocks, split 0 runs the update
 // the rest of that column exits.
+// One i per lane: six wavefronts per SIMD (the update's registers would allow
+// four; FP64 N = 3600 134.1 us per step with four, 128.9 with six).
 template <typename T, int MODE, int IPT, int WS>
-__global__ __launch_bounds__(pair_threads<WS>()) void k_pair_bh(PairArgs a, EpiArgs e) {
+__global__ __launch_bounds__(pair_threads<WS>(), IPT == 1 ? 6 : 4) void k_pair_bh(PairArgs a, EpiArgs e) {
   __shared__ double red[pair_red_doubles<T, IPT, WS>()];
   if (blockIdx.x == gridDim.x - 1) {
     if (blockIdx.y == 0) bh_final_block<double>(e);
