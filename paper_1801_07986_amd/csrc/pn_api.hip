@@ -63,6 +63,34 @@ int dual_splits(int Ns) {
   return std::max(1, std::min({24, Ns / 32, std::max(8, 6144 / iblocks)}));
 }
 
+constexpr int kCUs = 256;
+
+// j-splits of a sweep in workgroups of eight wavefronts.  Each CU runs its share
+// of the iblocks x splits workgroups, so the time goes with the largest share,
+// and in steps: N = 3000 (47 i-blocks), FP64, us per RK4 step: 16 splits (752
+// workgroups, 2.94 per CU) 94, 17 splits (3.12 per CU) 111.  The estimate is
+// that share times the j of a workgroup and what it spends besides (18 j: its
+// i-bodies, the sums over its wavefronts), a quarter of a workgroup for the end,
+// and the idle issue slots of one or two workgroups per CU (30 and 5 %:
+// N = 4097, 4 splits 176, 8 splits 138, 12 splits 134).  It picks the fastest
+// measured count, or one within 1 % of it, at N = 1200 to 30000 in both
+// precisions.  Counts for powers of two in between: N = 7000 FP64 361 instead of
+// 325, mixed 256 instead of 223; N = 2300 FP64 82 instead of 72.
+int fill_splits(int Ns, int iblocks, int ipt) {
+  if (iblocks >= 30 * kCUs / 16) return 16;  // shares of 30 and more even out by themselves
+  int best = 1;
+  double least = 0.0;
+  const int most = std::max(1, std::min(16, Ns / 32));
+  for (int ns = std::min(4, most); ns <= most; ++ns) {
+    const int64_t share = ((int64_t)iblocks * ns + kCUs - 1) / kCUs;
+    const double j = (double)((Ns + ns - 1) / ns);
+    const double idle = share == 1 ? 1.3 : share == 2 ? 1.05 : 1.0;
+    const double t = idle * (double)share * (j + 18.0 / ipt) + 0.25 * j;
+    if (least == 0.0 || t <= least) best = ns, least = t;
+  }
+  return best;
+}
+
 // Tuned shapes installed with pn_set_shape (searched by the autotuner).
 struct TunedShape {
   int precision;
@@ -71,7 +99,8 @@ struct TunedShape {
 };
 std::vector<TunedShape> g_tuned;
 
-// Shape: a tuned entry if one covers (precision, N), else the default: four
+// Shape: a tuned entry if one covers (precision, N; its j-splits 0: fill_splits
+// for eight wavefronts, else the default's), else the default: four
 // wavefronts per i-range, one i per lane, and 16 j-splits (measured best for
 // the whole evaluation at N = 16k-64k on MI355X: enough workgroups in flight
 // without making the epilogue's split reduction dominate), at least 32 j per
@@ -100,7 +129,9 @@ Shape pick_shape(int Ns, int precision) {
   }
   const int ib = (s.ws == 1 ? kBlock : 64) * s.ipt;  // i-bodies per workgroup
   s.iblocks = (Ns + ib - 1) / ib;
-  if (want_nsplit <= 0) {
+  if (want_nsplit <= 0 && s.ws == 8) {
+    want_nsplit = fill_splits(Ns, s.iblocks, s.ipt);
+  } else if (want_nsplit <= 0) {
     // default: about 4096 sweep workgroups, but at least 16 j per wavefront
     want_nsplit = std::max(16, (4096 + s.iblocks - 1) / s.iblocks);
     want_nsplit = std::min(want_nsplit, std::max(1, Ns / (16 * s.ws)));
@@ -625,7 +656,19 @@ int launch_bh_final(const EpiArgs& a, hipStream_t st) {
 
 template <typename T>
 void launch_pair_bh_t(const PairArgs& a, const EpiArgs& e, const Shape& sh, hipStream_t st) {
-  dim3 grid(sh.iblocks + 1, sh.nsplit);
+  // One i per lane: columns up to a multiple of the eight XCDs, where that does
+  // not add to the largest share of a CU: an i-block's workgroups then run on the
+  // XCD of the epilogue workgroup that reads their sums and writes their next
+  // packets (N = 3000 mixed 76.9 instead of 81.8 us per RK4 step, FP64 93.9
+  // instead of 97.9).  Two: one column more than a multiple of 64 (N = 16384 FP64
+  // 1489 instead of 1525: the splits of an i-block would all run on one XCD).
+  int gx = sh.iblocks % 64 == 0 ? sh.iblocks + 1 : sh.iblocks;
+  if (sh.ipt == 1) {
+    const auto share = [&](int64_t cols) { return (cols * sh.nsplit + kCUs - 1) / kCUs; };
+    gx = (sh.iblocks + 7) / 8 * 8;
+    if (share(gx) > share(sh.iblocks)) gx = sh.iblocks;
+  }
+  dim3 grid(gx, sh.nsplit + 1);
   if (sh.ws == 8) {
     if (sh.ipt == 2)
       hipLaunchKernelGGL((k_pair_bh<T, MODE_FUSED, 2, 8>), grid, dim3(2 * kBlock), 0, st, a, e);

@@ -1642,19 +1642,24 @@ __global__ __launch_bounds__(epi_threads<Dual>()) void k_epilogue_dual_bh(EpiArg
 // The sweep of a chained Runge-Kutta stage with the previous stage's
 // massive-object update (k_bh_final's work) in one extra workgroup: the sweep
 // reads only star packets, which the previous epilogue has written, so the
-// two are independent and the stage saves a kernel boundary.  Grid: the
-// sweep's (iblocks + 1) x nsplit; column iblocks, split 0 runs the update
-// the rest of that column exits.
+// two are independent and the stage saves a kernel boundary.  Grid:
+// (iblocks or a few columns more) x (1 + nsplit).  Row 0, column 0 runs the
+// update; the rest of that row and the columns beyond the stars exit at once.
+// The row comes first, so that the sweep's workgroups spread over the
+// CUs as if alone (as a last column its workgroups fell between them: a sweep
+// of 768 workgroups then did not fill 256 CUs evenly).
 // One i per lane: six wavefronts per SIMD (the update's registers would allow
 // four; FP64 N = 3600 134.1 us per step with four, 128.9 with six).
 template <typename T, int MODE, int IPT, int WS>
 __global__ __launch_bounds__(pair_threads<WS>(), IPT == 1 ? 6 : 4) void k_pair_bh(PairArgs a, EpiArgs e) {
   __shared__ double red[pair_red_doubles<T, IPT, WS>()];
-  if (blockIdx.x == gridDim.x - 1) {
-    if (blockIdx.y == 0) bh_final_block<double>(e);
+  if (blockIdx.y == 0) {
+    if (blockIdx.x == 0) bh_final_block<double>(e);
     return;
   }
-  pair_block<T, MODE, IPT, WS>(a, blockIdx.x, blockIdx.y, red);
+  constexpr int IB = pair_threads<WS>() / WS * IPT;  // i-bodies per workgroup
+  if ((int)blockIdx.x * IB >= a.Ns) return;
+  pair_block<T, MODE, IPT, WS>(a, blockIdx.x, blockIdx.y - 1, red);
 }
 
 // ---------------------------------------------------------------------------
