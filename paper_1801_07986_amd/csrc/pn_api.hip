@@ -224,7 +224,7 @@ Layout layout_for(int64_t N, const Shape& s, Need need, int stage_ns = 0) {
   L.bhpart2 = take(dual || fused ? nepi * 4 * W * sizeof(double) : 0);
   L.pk2 = take(fused ? Ns * sizeof(PkF64) : 0);
   L.bhs = take(fused ? 2 * kBhState * sizeof(double) : 0);
-  L.status = take(sizeof(int));
+  L.status = take(kStatusWords * sizeof(int));
   const size_t n3 = 3 * (size_t)N * sizeof(double);
   L.xs = take(rk4 ? n3 : 0);
   L.vs = take(rk4 ? n3 : 0);
@@ -259,15 +259,14 @@ TriPlan tri_plan(int Ns) {
   return T;
 }
 struct TriLayout {
-  size_t pk, srow, prow, out, total;
+  size_t pk, srow, prow, total;
 };
 TriLayout tri_layout(const TriPlan& T, int Ns, size_t packet) {
   TriLayout L;
   L.pk = 0;
   L.srow = align256(packet * Ns);
   L.prow = L.srow + align256((size_t)T.nb * 10 * sizeof(double));
-  L.out = L.prow + align256((size_t)T.nb * T.nchunk * kTriRow * sizeof(double));
-  L.total = L.out + align256(9 * sizeof(double));
+  L.total = L.prow + align256((size_t)T.nb * T.nchunk * kTriRow * sizeof(double));
   return L;
 }
 
@@ -336,7 +335,15 @@ struct DevState {
   // stream than the previous one waits for it (last_ev recorded on last_st)
   hipEvent_t last_ev = nullptr;
   hipStream_t last_st = nullptr;
+  // host memory that kernels write (calls that wait for their result only):
+  // status words, and eight doubles further on the results of pn_diagnostics
+  // and pn_encounters
+  void* host = nullptr;
+  bool host_used = false;  // kernels that write it were launched and not waited for
+  int* host_status() const { return static_cast<int*>(host); }
+  double* host_out() const { return static_cast<double*>(host) + 8; }
 };
+constexpr size_t kHostBytes = 32 * sizeof(double);
 std::vector<DevState> g_dev;
 
 double g_timing[3] = {0, 0, 0};
@@ -428,6 +435,7 @@ struct Sys {
 struct Ptrs {
   char* base;
   Layout L;
+  int* status = nullptr;  // the call's status words (begin_status)
   template <typename T>
   T* at(size_t off) const { return reinterpret_cast<T*>(base + off); }
 };
@@ -450,7 +458,7 @@ int launch_prologue(const Sys& s, const Ptrs& P, int precision, hipStream_t st,
   a.pk = P.at<void>(P.L.pk);
   a.ub = P.at<double>(P.L.ub);
   a.bpart = P.at<double>(P.L.bpart);
-  a.status = P.at<int>(P.L.status);
+  a.status = P.status;
   const int nb = (Ns + kBlock - 1) / kBlock;
   if (dual)
     hipLaunchKernelGGL(k_prologue<Dual>, dim3(nb), dim3(kBlock), 0, st, a);
@@ -576,7 +584,7 @@ EpiArgs epi_args(const Sys& s, const Ptrs& P, const Shape& sh, const Outs& o) {
   a.acc_1pn = o.acc_1pn;
   a.bhpart = P.at<double>(P.L.bhpart);
   a.nbepi = ne;
-  a.status = P.at<int>(P.L.status);
+  a.status = P.status;
   a.stage = o.stage;
   a.dt = o.dt;
   a.X = o.X;
@@ -1003,13 +1011,61 @@ int mark_call_end(DevState& d, hipStream_t st) {
   return PN_OK;
 }
 
-// Waits for st and reports the device status word of the call.
-int read_status(const Ptrs& P, hipStream_t st) {
-  int status = 0;
-  HIPCK(hipMemcpyAsync(&status, P.at<int>(P.L.status), sizeof(int), hipMemcpyDeviceToHost, st));
+// Before a call that has kernels write the host memory.  Every such call waits for
+// them (wait_host) unless a launch fails in between.
+int take_host(DevState& d) {
+  if (!d.host) {
+    hipError_t e = hipHostMalloc(&d.host, kHostBytes, hipHostMallocDefault);
+    if (e != hipSuccess) {
+      d.host = nullptr;
+      return fail_hip(e, "hipHostMalloc(status)", __LINE__);
+    }
+  }
+  if (d.host_used) HIPCK(hipDeviceSynchronize());
+  d.host_used = true;
+  return PN_OK;
+}
+
+int wait_host(DevState& d, hipStream_t st) {
   HIPCK(hipStreamSynchronize(st));
-  if (status & 2) return fail_inval("mass[0] must be positive and finite");
-  if (status & 1) return PN_ENONFINITE;
+  d.host_used = false;
+  return PN_OK;
+}
+
+// The status words of a call.  A call that waits takes the device's words in
+// host memory, which nothing else writes meanwhile (g_mu); one that does not
+// wait, or whose kernels may be in a step graph, takes words in its scratch,
+// cleared in stream order.
+int begin_status(DevState& d, Ptrs& P, hipStream_t st, int flags, bool steps = false) {
+  if (!(flags & PN_ASYNC)) {
+    int rc = take_host(d);
+    if (rc) return rc;
+    if (!steps) {
+      P.status = d.host_status();
+      for (int w = 0; w < kStatusWords; ++w) P.status[w] = 0;
+      return PN_OK;
+    }
+  }
+  P.status = P.at<int>(P.L.status);
+  hipLaunchKernelGGL(k_reset_status, dim3(1), dim3(64), 0, st, P.status);
+  HIPCK(hipGetLastError());
+  return PN_OK;
+}
+
+// Waits for st; the call's status words are in host memory then.
+int wait_status(DevState& d, const int* status, hipStream_t st) {
+  if (status != d.host_status()) {
+    hipLaunchKernelGGL(k_report_status, dim3(1), dim3(64), 0, st, status, d.host_status());
+    HIPCK(hipGetLastError());
+  }
+  return wait_host(d, st);
+}
+
+int read_status(DevState& d, const Ptrs& P, hipStream_t st) {
+  int rc = wait_status(d, P.status, st);
+  if (rc) return rc;
+  if (d.host_status()[kStatusMass]) return fail_inval("mass[0] must be positive and finite");
+  if (d.host_status()[kStatusNonfinite]) return PN_ENONFINITE;
   return PN_OK;
 }
 
@@ -1017,13 +1073,7 @@ int finish(DevState& d, const Ptrs& P, hipStream_t st, int flags) {
   int rc = mark_call_end(d, st);
   if (rc) return rc;
   if (flags & PN_ASYNC) return PN_OK;
-  return read_status(P, st);
-}
-
-int reset_status(const Ptrs& P, hipStream_t st) {
-  hipLaunchKernelGGL(k_reset_status, dim3(1), dim3(64), 0, st, P.at<int>(P.L.status));
-  HIPCK(hipGetLastError());
-  return PN_OK;
+  return read_status(d, P, st);
 }
 
 hipStream_t pick_stream(DevState& d, void* stream) {
@@ -1199,7 +1249,7 @@ BatchPlan plan_batch(int n_sys, const int64_t* off, int precision, const double*
   P.o_bpart = take((size_t)pro0 * kProRows * 8 * sizeof(double));
   P.o_part = take((size_t)part0 * sizeof(double));
   P.o_bhpart = take((size_t)epi0 * 4 * sizeof(double));
-  P.o_status = take(sizeof(int));
+  P.o_status = take(kStatusWords * sizeof(int));
   const size_t n3 = 3 * (size_t)P.n_bodies * sizeof(double);
   P.o_xs = take(n3);
   P.o_vs = take(n3);
@@ -1284,7 +1334,7 @@ int pn_potential_accel(const double* pos, const double* vel, const double* mass,
   hipStream_t st = pick_stream(*d, stream);
   if ((rc = order_after_previous(*d, st))) return rc;
   Sys s{pos, nullptr, mass, N, G, c, eps};
-  if ((rc = reset_status(P, st))) return rc;
+  if ((rc = begin_status(*d, P, st, flags))) return rc;
   if ((rc = launch_prologue(s, P, PN_FP64, st))) return rc;
   if ((rc = launch_pair(s, P, sh, PN_FP64, MODE_P1, st))) return rc;
   Outs o;
@@ -1311,7 +1361,7 @@ int pn_correction(const double* pos, const double* vel, const double* mass, int6
   hipStream_t st = pick_stream(*d, stream);
   if ((rc = order_after_previous(*d, st))) return rc;
   Sys s{pos, vel, mass, N, G, c, eps};
-  if ((rc = reset_status(P, st))) return rc;
+  if ((rc = begin_status(*d, P, st, flags))) return rc;
   if ((rc = launch_prologue(s, P, PN_FP64, st))) return rc;
   if ((rc = launch_pair(s, P, sh, PN_FP64, MODE_P2, st))) return rc;
   Outs o;
@@ -1345,7 +1395,7 @@ int pn_accel(const double* pos, const double* vel, const double* mass, int64_t N
   Timer tm;
   tm.d = d;
   tm.on = (flags & PN_TIMING) != 0;
-  if ((rc = reset_status(P, st))) return rc;
+  if ((rc = begin_status(*d, P, st, flags))) return rc;
   Outs o;
   o.acc_newton = acc_newton;
   o.phi = phi;
@@ -1390,14 +1440,14 @@ int pn_accel_noalloc(const double* pos, const double* vel, const double* mass, i
   Ptrs P{d->fixed, L};
   hipStream_t st = pick_stream(*d, stream);
   Sys s{pos, vel, mass, N, G, c, eps};
-  if ((rc = reset_status(P, st))) return rc;
+  if ((rc = begin_status(*d, P, st, flags))) return rc;
   Outs o;
   o.acc_newton = acc_newton;
   o.phi = phi;
   o.acc_1pn = acc_1pn;
   if ((rc = enqueue_eval(s, P, sh, precision, o, st, nullptr))) return rc;
   if (flags & PN_ASYNC) return PN_OK;
-  return read_status(P, st);
+  return read_status(*d, P, st);
 }
 
 int pn_accel_eih(const double* pos, const double* vel, const double* mass, int64_t N, double G,
@@ -1421,7 +1471,7 @@ int pn_accel_eih(const double* pos, const double* vel, const double* mass, int64
   Ptrs P{d->base, L};
   hipStream_t st = pick_stream(*d, stream);
   if ((rc = order_after_previous(*d, st))) return rc;
-  if ((rc = reset_status(P, st))) return rc;
+  if ((rc = begin_status(*d, P, st, flags))) return rc;
   EihArgs e;
   e.pos = pos;
   e.vel = vel;
@@ -1436,7 +1486,7 @@ int pn_accel_eih(const double* pos, const double* vel, const double* mass, int64
   e.acc_newton = acc_newton;
   e.phi = phi;
   e.acc_1pn = acc_1pn;
-  e.status = P.at<int>(L.status);
+  e.status = P.status;
   const int nb = (int)((N + kBlock - 1) / kBlock);
   Sys all{pos, vel, mass, N + 1, G, c, eps};  // launch_pair sweeps Ns = N bodies
   const bool mixed = precision == PN_MIXED;
@@ -1470,7 +1520,7 @@ int pn_step(double* pos, double* vel, const double* mass, int64_t N, double G, d
   hipStream_t st = pick_stream(*d, stream);
   if ((rc = order_after_previous(*d, st))) return rc;
   Sys s{pos, vel, mass, N, G, c, eps};
-  if ((rc = reset_status(P, st))) return rc;
+  if ((rc = begin_status(*d, P, st, flags, true))) return rc;
   const bool timing = (flags & PN_TIMING) != 0;
   const bool graph = !(flags & (PN_NOGRAPH | PN_TIMING));
   if (nsteps > 0 && ns > 0) {
@@ -1564,7 +1614,7 @@ int pn_jerk(const double* pos, const double* vel, const double* mass, int64_t N,
   hipStream_t st = pick_stream(*d, stream);
   if ((rc = order_after_previous(*d, st))) return rc;
   Sys s{pos, vel, mass, N, G, c, eps};
-  if ((rc = reset_status(P, st))) return rc;
+  if ((rc = begin_status(*d, P, st, flags))) return rc;
   Outs o;
   o.jerk = jerk;
   if ((rc = enqueue_jerk(s, P, sh, acc, o, st))) return rc;
@@ -1586,7 +1636,7 @@ int pn_step_hermite(double* pos, double* vel, const double* mass, int64_t N, dou
   hipStream_t st = pick_stream(*d, stream);
   if ((rc = order_after_previous(*d, st))) return rc;
   Sys s{pos, vel, mass, N, G, c, eps};
-  if ((rc = reset_status(P, st))) return rc;
+  if ((rc = begin_status(*d, P, st, flags, true))) return rc;
   if (nsteps > 0) {
     if ((rc = enqueue_hermite_start(s, P, sh, dt, pos, vel, st))) return rc;
     if (flags & (PN_NOGRAPH | PN_TIMING)) {
@@ -1633,6 +1683,7 @@ int pn_diagnostics(const double* pos, const double* vel, const double* mass, int
   char* base = d->base;
   hipStream_t st = pick_stream(*d, stream);
   if ((rc = order_after_previous(*d, st))) return rc;
+  if ((rc = take_host(*d))) return rc;
   DiagArgs a;
   a.pos = pos;
   a.vel = vel;
@@ -1646,7 +1697,7 @@ int pn_diagnostics(const double* pos, const double* vel, const double* mass, int
   a.nsrow = T.nb;
   a.prow = reinterpret_cast<double*>(base + L.prow);
   a.nprow = T.nb * T.nchunk;
-  a.out = reinterpret_cast<double*>(base + L.out);
+  a.out = d->host_out();
   const TriArgs t{Ns, T.jchunk, a.eps2, a.prow};
   hipLaunchKernelGGL(k_diag_stars, dim3(T.nb), dim3(kBlock), 0, st, a);
   HIPCK(hipGetLastError());
@@ -1654,12 +1705,10 @@ int pn_diagnostics(const double* pos, const double* vel, const double* mass, int
   HIPCK(hipGetLastError());
   hipLaunchKernelGGL(k_diag_final, dim3(1), dim3(kTriFinal), 0, st, a);
   HIPCK(hipGetLastError());
-  double got[9];  // the results and the status, one copy
-  HIPCK(hipMemcpyAsync(got, a.out, sizeof got, hipMemcpyDeviceToHost, st));
   if ((rc = mark_call_end(*d, st))) return rc;
-  HIPCK(hipStreamSynchronize(st));
-  memcpy(out8, got, 8 * sizeof(double));
-  if (got[8] != 0.0) return fail_inval("mass[0] must be positive and finite");
+  if ((rc = wait_host(*d, st))) return rc;
+  memcpy(out8, a.out, 8 * sizeof(double));
+  if (a.out[8] != 0.0) return fail_inval("mass[0] must be positive and finite");
   return PN_OK;
 }
 
@@ -1682,6 +1731,7 @@ int pn_encounters(const double* pos, const double* vel, const double* mass, int6
   char* base = d->base;
   hipStream_t st = pick_stream(*d, stream);
   if ((rc = order_after_previous(*d, st))) return rc;
+  if ((rc = take_host(*d))) return rc;
   EncArgs e;
   e.pos = pos;
   e.vel = vel;
@@ -1695,7 +1745,7 @@ int pn_encounters(const double* pos, const double* vel, const double* mass, int6
   e.nsrow = T.nb;
   e.prow = reinterpret_cast<double*>(base + L.prow);
   e.nprow = T.nb * T.nchunk;
-  e.out = reinterpret_cast<double*>(base + L.out);
+  e.out = d->host_out();
   const TriArgs t{Ns, T.jchunk, 0.0, e.prow};
   hipLaunchKernelGGL(k_enc_stars, dim3(T.nb), dim3(kBlock), 0, st, e);
   HIPCK(hipGetLastError());
@@ -1703,9 +1753,9 @@ int pn_encounters(const double* pos, const double* vel, const double* mass, int6
   HIPCK(hipGetLastError());
   hipLaunchKernelGGL(k_enc_final, dim3(1), dim3(kTriFinal), 0, st, e);
   HIPCK(hipGetLastError());
-  HIPCK(hipMemcpyAsync(out8, e.out, 8 * sizeof(double), hipMemcpyDeviceToHost, st));
   if ((rc = mark_call_end(*d, st))) return rc;
-  HIPCK(hipStreamSynchronize(st));
+  if ((rc = wait_host(*d, st))) return rc;
+  memcpy(out8, e.out, 8 * sizeof(double));
   return PN_OK;
 }
 
@@ -1766,6 +1816,7 @@ int pn_step_batched(int32_t n_sys, const int64_t* offsets, const double* G, cons
     d->bdesc_valid = true;
     d->basked_steps = 0;
   }
+  if (!(flags & PN_ASYNC) && (rc = take_host(*d))) return rc;
   hipLaunchKernelGGL(k_reset_status, dim3(1), dim3(64), 0, st, status);
   HIPCK(hipGetLastError());
   if (nsteps > 0) {
@@ -1795,11 +1846,10 @@ int pn_step_batched(int32_t n_sys, const int64_t* offsets, const double* G, cons
   }
   if ((rc = mark_call_end(*d, st))) return rc;
   if (flags & PN_ASYNC) return PN_OK;
-  int hstatus = 0;
-  HIPCK(hipMemcpyAsync(&hstatus, status, sizeof(int), hipMemcpyDeviceToHost, st));
-  HIPCK(hipStreamSynchronize(st));
-  if (hstatus & 2) return fail_inval("mass of a massive object must be positive and finite");
-  if (hstatus & 1) return PN_ENONFINITE;
+  if ((rc = wait_status(*d, status, st))) return rc;
+  if (d->host_status()[kStatusMass])
+    return fail_inval("mass of a massive object must be positive and finite");
+  if (d->host_status()[kStatusNonfinite]) return PN_ENONFINITE;
   return PN_OK;
 }
 
