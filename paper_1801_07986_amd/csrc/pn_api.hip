@@ -51,44 +51,50 @@ struct Shape {
   int dsplit = 1;  // j splits of the jerk sweep
   int djchunk = 1; // j per split there
 };
-// j splits of the jerk sweep (64 i-bodies and 4 wavefronts per workgroup, at
-// most 4 workgroups resident per CU): 24, which is fastest or within 1 % of it
-// from N = 1024 to 16384 (N = 2048: 60.9 us per Hermite step, 69.7 with 12;
-// 8192: 405 and 418; 16384: 1452 and 1467), fewer where a wavefront would get
-// less than 8 j (N = 300: 31.6 with 8 or 9, 33.9 with 24), and no more than
-// give 6144 workgroups where there are many i-bodies (the partial sums grow
-// with the splits), 8 at least.
-int dual_splits(int Ns) {
-  const int iblocks = (Ns + 63) / 64;
-  return std::max(1, std::min({24, Ns / 32, std::max(8, 6144 / iblocks)}));
-}
-
 constexpr int kCUs = 256;
 
-// j-splits of a sweep in workgroups of eight wavefronts.  Each CU runs its share
-// of the iblocks x splits workgroups, so the time goes with the largest share,
-// and in steps: N = 3000 (47 i-blocks), FP64, us per RK4 step: 16 splits (752
+// j-splits of a sweep, from `least` to `most`.  Each CU runs its share of the
+// iblocks x splits workgroups, so the time goes with the largest share, and in
+// steps: N = 3000 (47 i-blocks), FP64, us per RK4 step: 16 splits (752
 // workgroups, 2.94 per CU) 94, 17 splits (3.12 per CU) 111.  The estimate is
-// that share times the j of a workgroup and what it spends besides (18 j: its
-// i-bodies, the sums over its wavefronts), a quarter of a workgroup for the end,
-// and the idle issue slots of one or two workgroups per CU (30 and 5 %:
-// N = 4097, 4 splits 176, 8 splits 138, 12 splits 134).  It picks the fastest
-// measured count, or one within 1 % of it, at N = 1200 to 30000 in both
-// precisions.  Counts for powers of two in between: N = 7000 FP64 361 instead of
-// 325, mixed 256 instead of 223; N = 2300 FP64 82 instead of 72.
-int fill_splits(int Ns, int iblocks, int ipt) {
-  if (iblocks >= 30 * kCUs / 16) return 16;  // shares of 30 and more even out by themselves
+// that share times the j of a workgroup and what it spends besides (`own`, in j:
+// its i-bodies, the sums over its wavefronts), a quarter of a workgroup for the
+// end, and the idle issue slots of one or two workgroups per CU (idle1, idle2).
+int fill_splits(int Ns, int iblocks, int least, int most, double own, double idle1,
+                double idle2) {
   int best = 1;
-  double least = 0.0;
-  const int most = std::max(1, std::min(16, Ns / 32));
-  for (int ns = std::min(4, most); ns <= most; ++ns) {
+  double time = 0.0;
+  most = std::max(1, most);
+  for (int ns = std::min(least, most); ns <= most; ++ns) {
     const int64_t share = ((int64_t)iblocks * ns + kCUs - 1) / kCUs;
     const double j = (double)((Ns + ns - 1) / ns);
-    const double idle = share == 1 ? 1.3 : share == 2 ? 1.05 : 1.0;
-    const double t = idle * (double)share * (j + 18.0 / ipt) + 0.25 * j;
-    if (least == 0.0 || t <= least) best = ns, least = t;
+    const double idle = share == 1 ? idle1 : share == 2 ? idle2 : 1.0;
+    const double t = idle * (double)share * (j + own) + 0.25 * j;
+    if (time == 0.0 || t <= time) best = ns, time = t;
   }
   return best;
+}
+
+// Eight wavefronts per workgroup: 4 to 16 splits.  Idle slots: N = 4097, 4 splits
+// (one workgroup per CU) 176 us per FP64 step, 8 splits 138, 12 splits 134.  The
+// estimate picks the fastest measured count, or one within 1 % of it, at N = 1200
+// to 30000 in both precisions.  Counts for powers of two in between: N = 7000 FP64
+// 361 instead of 325, mixed 256 instead of 223; N = 2300 FP64 82 instead of 72.
+int sweep_splits(int Ns, int iblocks, int ipt) {
+  if (iblocks >= 30 * kCUs / 16) return 16;  // shares of 30 and more even out by themselves
+  return fill_splits(Ns, iblocks, 4, std::min(16, Ns / 32), 18.0 / ipt, 1.3, 1.05);
+}
+
+// The jerk sweep (64 i-bodies and 4 wavefronts per workgroup, at most 4 of them
+// resident per CU): up to 24 splits, at least 8 j per wavefront, and no more than
+// give 6144 workgroups where there are many i-bodies (the partial sums grow with
+// the splits), 8 at least.  us per Hermite step with as many as that and with the
+// estimate's: N = 1200 43.7, 41.1; 2300 65.8, 61.7; 3000 88.3, 82.5; 5000 173.4,
+// 168.5; from 7000 on within 1 %.
+int dual_splits(int Ns) {
+  const int iblocks = (Ns + 63) / 64;
+  const int most = std::min({24, Ns / 32, std::max(8, 6144 / iblocks)});
+  return fill_splits(Ns, iblocks, 8, most, 8.0, 1.1, 1.1);
 }
 
 // Tuned shapes installed with pn_set_shape (searched by the autotuner).
@@ -99,7 +105,7 @@ struct TunedShape {
 };
 std::vector<TunedShape> g_tuned;
 
-// Shape: a tuned entry if one covers (precision, N; its j-splits 0: fill_splits
+// Shape: a tuned entry if one covers (precision, N; its j-splits 0: sweep_splits
 // for eight wavefronts, else the default's), else the default: four
 // wavefronts per i-range, one i per lane, and 16 j-splits (measured best for
 // the whole evaluation at N = 16k-64k on MI355X: enough workgroups in flight
@@ -130,7 +136,7 @@ Shape pick_shape(int Ns, int precision) {
   const int ib = (s.ws == 1 ? kBlock : 64) * s.ipt;  // i-bodies per workgroup
   s.iblocks = (Ns + ib - 1) / ib;
   if (want_nsplit <= 0 && s.ws == 8) {
-    want_nsplit = fill_splits(Ns, s.iblocks, s.ipt);
+    want_nsplit = sweep_splits(Ns, s.iblocks, s.ipt);
   } else if (want_nsplit <= 0) {
     // default: about 4096 sweep workgroups, but at least 16 j per wavefront
     want_nsplit = std::max(16, (4096 + s.iblocks - 1) / s.iblocks);
