@@ -1173,9 +1173,16 @@ struct BatchPlan {
 
 // Shapes, partial-sum slots and launch prefixes of an ensemble.  Every
 // system uses one sweep shape: IPT i-bodies per lane (the installed batched
-// shape of the precision, default 1), 4 wavefronts per i-range; the number of
-// j-splits is common, by default chosen so the whole ensemble has ~16k sweep
-// workgroups, and capped per system so each wavefront keeps at least 32 j.
+// shape of the precision, default 1), 4 wavefronts per i-range.  The number of
+// j-splits is common, and capped per system so each wavefront keeps at least 32
+// j: without an installed one, what gives the whole ensemble about 8192 sweep
+// workgroups of one i per lane (half as many of two), 2 at least (more only cost
+// partial sums: 256 systems, 2.3 million bodies) and 8 at most.  With two splits
+// for every ensemble the last workgroups ran alone.  us per step with two and
+// with the rule's, FP64 and mixed: 8 systems of 2048 to 8192 bodies 2004 and
+// 1283, 1696 and 1087; 6 of 12000 to 16384 7543 and 4770, 6816 and 4184; 24 of 2048
+// to 16384 14528 and 8863, 14382 and 8762; 64 of 1000 to 8000 and 100 of 200 to
+// 2000 the same within 1 %, mixed 100 770 and 751.
 // PN_BATCH_SHAPE="ipt,nsplit" overrides the shape (tuning runs).
 // (G, c, eps may be null when only the shape is wanted)
 BatchPlan plan_batch(int n_sys, const int64_t* off, int precision, const double* G = nullptr,
@@ -1194,8 +1201,9 @@ BatchPlan plan_batch(int n_sys, const int64_t* off, int precision, const double*
   const int ib = 64 * P.ipt;  // i-bodies per sweep workgroup
   int64_t tot_iblocks = 0;
   for (int b = 0; b < n_sys; ++b) tot_iblocks += (off[b + 1] - off[b] - 1 + ib - 1) / ib;
+  const int64_t want = 8192 / P.ipt;
   int ns_common =
-      (int)std::max<int64_t>(1, std::min<int64_t>(16, (16384 + tot_iblocks - 1) / tot_iblocks));
+      (int)std::max<int64_t>(2, std::min<int64_t>(8, (want + tot_iblocks - 1) / tot_iblocks));
   if (bs.nsplit > 0) ns_common = bs.nsplit;
   P.splits = ns_common;
   int64_t star0 = 0, part0 = 0;
