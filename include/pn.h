@@ -233,10 +233,11 @@ int pn_step_batched(int32_t n_sys, const int64_t* offsets, const double* G, cons
 /*
  * Sweep shape of pn_step_batched in the given precision (searched by the
  * autotuner over whole ensemble steps): ipt i-bodies per lane (1 or 2) for
- * every system, and the ensemble's common j-split count (1..64; 0 = the
- * default rule, about 16k sweep workgroups in all), which each system caps so
- * that a wavefront keeps at least 32 j.  precision < 0 restores the defaults
- * (1 i per lane, the rule).  Like pn_set_shape, it changes speed only.
+ * every system, and the ensemble's common j-split count (1..64; 0 = about 16k
+ * sweep workgroups in all), which each system caps so that a wavefront keeps at
+ * least 32 j.  precision < 0 restores the defaults (FP64 2 i per lane, mixed 1,
+ * and 2 to 8 splits by the number of i-ranges).  Like pn_set_shape, it changes
+ * speed only.
  */
 int pn_set_batch_shape(int precision, int ipt, int nsplit);
 
@@ -276,7 +277,8 @@ int pn_query_stage_kernel(int precision, int64_t N);
  * the given precision (searched by the autotuner; later entries never override
  * earlier ones that match).  ipt: i-bodies per lane (1 or 2); ws: wavefronts
  * sharing one i-range (1, 4, or 8 in workgroups of 512 threads); nsplit: j-range
- * splits (0 = default rule).
+ * splits (0 = default rule; for 8 wavefronts the count, 4 to 16, that loads
+ * the GPU's CUs most evenly).
  * precision < 0 clears the table.  Shapes change speed only: results of a
  * given shape are deterministic and every shape meets the same accuracy.
  */
@@ -302,7 +304,8 @@ const char* pn_strerror(int code);
  */
 int pn_last_timing(double* out);
 
-/* Frees the library's scratch memory and cached graphs on every device. */
+/* Frees the library's scratch memory, cached graphs and pinned host words on
+ * every device. */
 int pn_release(void);
 
 #ifdef __cplusplus

@@ -1153,13 +1153,14 @@ int run_steps(DevState& d, const GraphKey& key, int64_t nsteps, hipStream_t st,
 }
 
 // ------------------------------------------------------------------ batched ensembles
-// Batched sweep shape per precision (pn_set_batch_shape, from the
-// autotuner's table): i-bodies per lane of every system, and the common
-// j-split count (0: the rule in plan_batch).
+// Batched sweep shape per precision (pn_set_batch_shape; the autotuner's table
+// may hold one): i-bodies per lane of every system, and the common j-split
+// count (0, -1: the rules in plan_batch; -1: no shape was set).
 struct BatchShape {
-  int ipt = 1, nsplit = 0;
+  int ipt, nsplit;
 };
-BatchShape g_batch_shape[2];
+constexpr BatchShape kBatchDefault[2] = {{2, -1}, {1, -1}};  // FP64, mixed
+BatchShape g_batch_shape[2] = {kBatchDefault[0], kBatchDefault[1]};
 
 struct BatchPlan {
   std::vector<SysDev> sys;
@@ -1172,12 +1173,13 @@ struct BatchPlan {
 };
 
 // Shapes, partial-sum slots and launch prefixes of an ensemble.  Every
-// system uses one sweep shape: IPT i-bodies per lane (the installed batched
-// shape of the precision, default 1), 4 wavefronts per i-range.  The number of
-// j-splits is common, and capped per system so each wavefront keeps at least 32
-// j: without an installed one, what gives the whole ensemble about 8192 sweep
-// workgroups of one i per lane (half as many of two), 2 at least (more only cost
-// partial sums: 256 systems, 2.3 million bodies) and 8 at most.  With two splits
+// system uses one sweep shape: IPT i-bodies per lane (FP64 2, mixed 1: 256
+// systems of 2.3 million bodies 143.7 and 86.3 ms per step, the other way 146.7
+// and 91.5), 4 wavefronts per i-range.  The number of j-splits is common, and
+// capped per system so each wavefront keeps at least 32 j: without a shape set,
+// what gives the whole ensemble about 8192 sweep workgroups of one i per lane
+// (half as many of two), 2 at least (more only cost partial sums there) and 8 at
+// most; set to 0, what gives 16384 workgroups, 16 at most.  With two splits
 // for every ensemble the last workgroups ran alone.  us per step with two and
 // with the rule's, FP64 and mixed: 8 systems of 2048 to 8192 bodies 2004 and
 // 1283, 1696 and 1087; 6 of 12000 to 16384 7543 and 4770, 6816 and 4184; 24 of 2048
@@ -1201,10 +1203,12 @@ BatchPlan plan_batch(int n_sys, const int64_t* off, int precision, const double*
   const int ib = 64 * P.ipt;  // i-bodies per sweep workgroup
   int64_t tot_iblocks = 0;
   for (int b = 0; b < n_sys; ++b) tot_iblocks += (off[b + 1] - off[b] - 1 + ib - 1) / ib;
-  const int64_t want = 8192 / P.ipt;
-  int ns_common =
-      (int)std::max<int64_t>(2, std::min<int64_t>(8, (want + tot_iblocks - 1) / tot_iblocks));
-  if (bs.nsplit > 0) ns_common = bs.nsplit;
+  const auto splits_for = [&](int64_t wgs) { return (wgs + tot_iblocks - 1) / tot_iblocks; };
+  int ns_common = bs.nsplit;
+  if (bs.nsplit == 0)
+    ns_common = (int)std::max<int64_t>(1, std::min<int64_t>(16, splits_for(16384)));
+  else if (bs.nsplit < 0)
+    ns_common = (int)std::max<int64_t>(2, std::min<int64_t>(8, splits_for(8192 / P.ipt)));
   P.splits = ns_common;
   int64_t star0 = 0, part0 = 0;
   int pro0 = 0, epi0 = 0;
@@ -1915,7 +1919,7 @@ int pn_query_stage_kernel(int precision, int64_t N) {
 int pn_set_batch_shape(int precision, int ipt, int nsplit) {
   std::lock_guard<std::mutex> lk(g_mu);
   if (precision < 0) {
-    g_batch_shape[0] = g_batch_shape[1] = BatchShape();
+    for (int p = 0; p < 2; ++p) g_batch_shape[p] = kBatchDefault[p];
     return PN_OK;
   }
   if ((precision != PN_FP64 && precision != PN_MIXED) || (ipt != 1 && ipt != 2) || nsplit < 0 ||
@@ -1984,6 +1988,9 @@ int pn_release(void) {
     if (d.base) (void)hipFree(d.base);
     d.base = nullptr;
     d.cap = 0;
+    if (d.host) (void)hipHostFree(d.host);
+    d.host = nullptr;
+    d.host_used = false;
     if (d.own) (void)hipStreamDestroy(d.own);
     d.own = nullptr;
     d.init = false;

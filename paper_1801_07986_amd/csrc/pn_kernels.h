@@ -37,7 +37,7 @@
 // For small systems k_stage runs a whole stage in one launch (each workgroup
 // sums all j for a few stars and runs their epilogue; every workgroup
 // recomputes the massive object's pending update), four kernels per step.
-// All reductions of the O(N) kernels are wavefront xor butterflies.
+// Sums over a wavefront are folds or xor butterflies.
 //
 // The same four kernels instantiated on dual numbers (T = S = Dual) give the
 // time derivative of the force along the motion (the jerk of the Hermite
@@ -455,7 +455,7 @@ __device__ __forceinline__ void wave_sum(double (&v)[K]) {
 }
 
 // Sum of `rows` partial rows of width `stride` (first K columns), fixed order:
-// lane l of every wavefront sums rows l, l+64, ..., then wave_allsum.  Every
+// lane l of every wavefront sums rows l, l+64, ..., then wave_sum.  Every
 // thread of every workgroup ends with the same bits, without a barrier.
 // Split in two so that a kernel can request the rows of several sums before
 // waiting for any: rows_load (this lane's partial sums), then rows_sum.
