@@ -104,13 +104,18 @@ def tune(sizes, log=print, precisions=PRECISIONS):
         for prec_name, prec in (("fp64", pn.PN_FP64), ("mixed", pn.PN_MIXED)):
             if prec_name not in precisions:
                 continue
-            best = None
+            best = rule = None
             for ipt, ws, ns in candidates(N):
                 os.environ["PN_SHAPE"] = f"{ipt},{ws},{ns}"
                 ms = time_step(pn, torch, P, V, Mm, prec)
                 log(f"[autotune]   N={N} {prec_name} ipt={ipt} ws={ws} nsplit={ns}: {ms:.4f} ms/step")
                 if best is None or ms < best[0]:
                     best = (ms, ipt, ws, ns)
+                if ws == 8 and ns == 0 and N >= 2048 and (rule is None or ms < rule[0]):
+                    rule = (ms, ipt, ws, ns)
+            # the rule's split counts hold between the measured sizes, too
+            if rule is not None and rule[0] <= 1.02 * best[0]:
+                best = rule
             os.environ.pop("PN_SHAPE", None)
             default_ms = time_step(pn, torch, P, V, Mm, prec)
             ms, ipt, ws, ns = best
