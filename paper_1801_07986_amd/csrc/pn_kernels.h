@@ -908,7 +908,7 @@ __device__ __forceinline__ void pair_block(const PairArgs& a, int ib, int sp, do
   // (one line then; with all of them N = 65536 mixed takes 0.5 % longer).
   const int run = (j1 - j0) * (int)sizeof(Pk);
   const unsigned touched = *reinterpret_cast<const unsigned*>(
-      reinterpret_cast<const char*>(pk + j0) +
+      reinterpret_cast<const char*>(pk + min(j0, a.Ns - 1)) +  // (no j: some packet)
       min((run <= 2 * 64 * 128 ? 128 : 0) * (int)(threadIdx.x & 63), max(0, run - 4)));
   PairI<T, IPT> I;
 #pragma unroll
