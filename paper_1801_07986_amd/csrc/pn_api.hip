@@ -251,14 +251,16 @@ Layout layout_for(int64_t N, const Shape& s, Need need, int stage_ns = 0) {
 // its last round of workgroups being nearly empty.  A chunk keeps at least 16
 // j (where launches are all that counts: 42.8 us a call at N = 100 against 52
 // with 64), 64 from N = 4096 on (N = 10001: 127 us against 136 with 32, whose
-// rows the last kernel sums).
+// rows the last kernel sums), and 128 from N = 12800 on (both calls, N = 16384:
+// 367 us against 384 with 64; 20000: 400 and 407; at 9000 and 12000 they are 1 to 3 %
+// slower with as many).
 struct TriPlan {
   int nb, nchunk, jchunk;
 };
 TriPlan tri_plan(int Ns) {
   TriPlan T;
   T.nb = (Ns + kBlock - 1) / kBlock;
-  const int least = std::max(16, std::min(64, Ns / 64));
+  const int least = Ns < 12800 ? std::max(16, std::min(64, Ns / 64)) : 128;
   const int want = std::max(1, std::min(2 * 8192 / T.nb, (Ns + least - 1) / least));
   T.jchunk = (Ns + want - 1) / want;
   T.nchunk = (Ns + T.jchunk - 1) / T.jchunk;
