@@ -1103,6 +1103,30 @@ constexpr int kStepsPerGraph = 16;
 // nothing from N = 10001 on, where the launches hide behind the sweeps).
 constexpr int64_t kGraphAfterSteps = 256;
 
+// What a step graph was captured for: the caller's buffers and parameters, and
+// what decides its kernels and where its buffers lie in the scratch memory (the
+// launch shape also for one-launch stages: the split count moves them).
+GraphKey graph_key(const Sys& s, const Shape& sh, double dt, int precision, int stage_ns,
+                   int scheme, char* base) {
+  GraphKey key;
+  key.pos = s.pos;
+  key.vel = s.vel;
+  key.mass = s.mass;
+  key.N = s.N;
+  key.G = s.G;
+  key.c = s.c;
+  key.eps = s.eps;
+  key.dt = dt;
+  key.precision = precision;
+  key.ipt = sh.ipt;
+  key.ws = sh.ws;
+  key.nsplit = sh.nsplit;
+  key.stage_ns = stage_ns;
+  key.scheme = scheme;
+  key.base = base;
+  return key;
+}
+
 // Captures `steps` time steps (on the library's own stream) into *graph/*exec.
 template <typename Enqueue>
 int capture_steps(DevState& d, int steps, Enqueue& enqueue_step, hipGraph_t* graph,
@@ -1557,18 +1581,7 @@ int pn_step(double* pos, double* vel, const double* mass, int64_t N, double G, d
           if ((rc = enqueue_stage_step(s, P, sh, precision, dt, pos, vel, ns, false, st, &tm)))
             return rc;
       } else {
-        GraphKey key;
-        key.pos = pos;
-        key.vel = vel;
-        key.mass = mass;
-        key.N = N;
-        key.G = G;
-        key.c = c;
-        key.eps = eps;
-        key.dt = dt;
-        key.precision = precision;
-        key.stage_ns = ns;
-        key.base = d->base;
+        const GraphKey key = graph_key(s, sh, dt, precision, ns, 0, d->base);
         rc = run_steps(*d, key, nsteps - 1, st, [&](hipStream_t cs) {
           return enqueue_stage_step(s, P, sh, precision, dt, pos, vel, ns, false, cs, nullptr);
         });
@@ -1589,20 +1602,7 @@ int pn_step(double* pos, double* vel, const double* mass, int64_t N, double G, d
           return rc;
       if ((rc = tm.collect((double)(N - 1) * (double)(N - 2)))) return rc;
     } else {
-      GraphKey key;
-      key.pos = pos;
-      key.vel = vel;
-      key.mass = mass;
-      key.N = N;
-      key.G = G;
-      key.c = c;
-      key.eps = eps;
-      key.dt = dt;
-      key.precision = precision;
-      key.ipt = sh.ipt;
-      key.ws = sh.ws;
-      key.nsplit = sh.nsplit;
-      key.base = d->base;
+      const GraphKey key = graph_key(s, sh, dt, precision, 0, 0, d->base);
       // the first sweep, nsteps - 1 steps (each ending in the next step's first
       // sweep), and the last step
       if ((rc = enqueue_rk4_head(s, P, sh, precision, dt, pos, vel, st, nullptr))) return rc;
@@ -1663,21 +1663,7 @@ int pn_step_hermite(double* pos, double* vel, const double* mass, int64_t N, dou
       for (int64_t k = 0; k < nsteps; ++k)
         if ((rc = enqueue_hermite_step(s, P, sh, dt, pos, vel, st))) return rc;
     } else {
-      GraphKey key;
-      key.scheme = 1;
-      key.pos = pos;
-      key.vel = vel;
-      key.mass = mass;
-      key.N = N;
-      key.G = G;
-      key.c = c;
-      key.eps = eps;
-      key.dt = dt;
-      key.precision = PN_FP64;
-      key.ipt = sh.ipt;
-      key.ws = sh.ws;
-      key.nsplit = sh.nsplit;
-      key.base = d->base;
+      const GraphKey key = graph_key(s, sh, dt, PN_FP64, 0, 1, d->base);
       rc = run_steps(*d, key, nsteps, st, [&](hipStream_t cs) {
         return enqueue_hermite_step(s, P, sh, dt, pos, vel, cs);
       });
