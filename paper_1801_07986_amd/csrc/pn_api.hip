@@ -343,7 +343,7 @@ struct DevState {
   // stream than the previous one waits for it (last_ev recorded on last_st)
   hipEvent_t last_ev = nullptr;
   hipStream_t last_st = nullptr;
-  // host memory that kernels write (calls that wait for their result only):
+  // pinned host memory that kernels write (calls that wait for their result only):
   // status words, and eight doubles further on the results of pn_diagnostics
   // and pn_encounters
   void* host = nullptr;
@@ -362,6 +362,14 @@ int dev_state(DevState** out) {
   if ((int)g_dev.size() <= dev) g_dev.resize(dev + 1);
   DevState& d = g_dev[dev];
   if (!d.init) {
+    // (here, not at the first call that waits, which may be pn_accel_noalloc)
+    if (!d.host) {
+      hipError_t e = hipHostMalloc(&d.host, kHostBytes, hipHostMallocDefault);
+      if (e != hipSuccess) {
+        d.host = nullptr;
+        return fail_hip(e, "hipHostMalloc(status)", __LINE__);
+      }
+    }
     HIPCK(hipStreamCreateWithFlags(&d.own, hipStreamDefault));
     void* fixed = nullptr;
     HIPCK(hipGetSymbolAddress(&fixed, HIP_SYMBOL(scratch)));
@@ -1022,13 +1030,6 @@ int mark_call_end(DevState& d, hipStream_t st) {
 // Before a call that has kernels write the host memory.  Every such call waits for
 // them (wait_host) unless a launch fails in between.
 int take_host(DevState& d) {
-  if (!d.host) {
-    hipError_t e = hipHostMalloc(&d.host, kHostBytes, hipHostMallocDefault);
-    if (e != hipSuccess) {
-      d.host = nullptr;
-      return fail_hip(e, "hipHostMalloc(status)", __LINE__);
-    }
-  }
   if (d.host_used) HIPCK(hipDeviceSynchronize());
   d.host_used = true;
   return PN_OK;

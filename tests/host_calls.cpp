@@ -201,8 +201,29 @@ void check_stage_shape() {
   }
 }
 
+// pn_accel_noalloc allocates and frees nothing once the device is set up, by
+// whichever call: the first of all, and the first after pn_release.
+void check_noalloc() {
+  System a(300);
+  std::vector<double> acc(3 * a.N), phi(a.N), acc1(3 * a.N);
+  const auto eval = [&](auto* f, int flags) {
+    return f(a.pos.data(), a.vel.data(), a.mass.data(), a.N, G, C, EPS, PN_FP64, acc.data(),
+             phi.data(), acc1.data(), nullptr, flags);
+  };
+  for (int round = 0; round < 2; ++round) {
+    EXPECT(eval(round ? pn_accel_noalloc : pn_accel, PN_ASYNC) == PN_OK);  // sets the device up
+    const Counts before = count;
+    for (int flags : {0, PN_ASYNC, 0}) EXPECT(eval(pn_accel_noalloc, flags) == PN_OK);
+    EXPECT(count.device == before.device && count.host == before.host &&
+           count.freed == before.freed);
+    EXPECT(pn_release() == PN_OK);
+  }
+  EXPECT(count.host == 2);
+}
+
 int main(int argc, char** argv) {
   const std::map<std::string, void (*)()> checks = {
+      {"noalloc", check_noalloc},
       {"stage_shape", check_stage_shape},
   };
   if (argc != 2 || !checks.count(argv[1])) return 2;
