@@ -32,7 +32,10 @@
  *   call returns, except inside the cached step graphs of pn_step,
  *   pn_step_hermite (16 steps per replay) and pn_step_batched.  A graph is
  *   captured once 256 steps in a row were asked for with the same pointers and
- *   parameters, and used for those only; other steps are launched directly.
+ *   parameters, in one call or several (calls with PN_NOGRAPH or PN_TIMING do
+ *   not count), by the first call that can replay it (at least 17 steps of
+ *   pn_step, 16 of pn_step_hermite), and used for those pointers and parameters
+ *   only; other steps are launched directly.
  * - Return codes: PN_OK, or one of the negative codes below.  No C++ exception
  *   crosses the ABI.  Outputs are unspecified after an error, except
  *   PN_ENONFINITE, where all outputs are written.

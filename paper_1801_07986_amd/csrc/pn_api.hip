@@ -1096,8 +1096,10 @@ hipStream_t pick_stream(DevState& d, void* stream) {
 constexpr int kStepsPerGraph = 16;
 
 // The graph is captured once this many steps have been asked for in a row with
-// one set of buffers and parameters (in one call or several); until then, and
-// for steps left over, the kernels are launched directly.  Capturing takes
+// one set of buffers and parameters (in one call or several that allow graphs;
+// every step a caller asks for counts), by the first call that has steps enough
+// to replay it; until then, and for steps left over, the kernels are launched
+// directly.  Capturing takes
 // 230-350 us (N = 1024: 32 steps on new buffers 1856 us launched directly, 2099
 // with the capture; N = 3000, mixed, 8 steps: 774 and 1033), and replaying saves
 // at most 1.4 us a step (N = 1024: 52.0 against 53.4 us; N = 100: 36.1 and 36.3;
@@ -1154,19 +1156,20 @@ int capture_steps(DevState& d, int steps, Enqueue& enqueue_step, hipGraph_t* gra
   return PN_OK;
 }
 
-// Enqueues nsteps time steps on `st`: by replays of the captured graph where
-// one is cached for this key or worth capturing, the rest directly.  The steps
-// and their order are the same, so are the results.
+// Enqueues nsteps time steps on `st`, of a call that asked for `asked` steps
+// (pn_step launches the first or last itself): by replays of the captured graph
+// where one is cached for this key or worth capturing, the rest directly.  The
+// steps and their order are the same, so are the results.
 template <typename Enqueue>
-int run_steps(DevState& d, const GraphKey& key, int64_t nsteps, hipStream_t st,
+int run_steps(DevState& d, const GraphKey& key, int64_t asked, int64_t nsteps, hipStream_t st,
               Enqueue enqueue_step) {
   int rc;
   if (!(key == d.asked)) {
     d.asked = key;
     d.asked_steps = 0;
   }
-  d.asked_steps += nsteps;
-  if (d.asked_steps >= kGraphAfterSteps && !(key == d.key)) {
+  d.asked_steps += asked;
+  if (d.asked_steps >= kGraphAfterSteps && nsteps >= kStepsPerGraph && !(key == d.key)) {
     drop_graph(d);
     if ((rc = capture_steps(d, kStepsPerGraph, enqueue_step, &d.graph, &d.gexec))) return rc;
     d.key = key;
@@ -1576,18 +1579,16 @@ int pn_step(double* pos, double* vel, const double* mass, int64_t N, double G, d
     tm.on = timing;
     if ((rc = launch_stage_head(s, P, sh, precision, ns, st))) return rc;
     if ((rc = enqueue_stage_step(s, P, sh, precision, dt, pos, vel, ns, true, st, &tm))) return rc;
-    if (nsteps > 1) {
-      if (!graph) {
-        for (int64_t k = 1; k < nsteps; ++k)
-          if ((rc = enqueue_stage_step(s, P, sh, precision, dt, pos, vel, ns, false, st, &tm)))
-            return rc;
-      } else {
-        const GraphKey key = graph_key(s, sh, dt, precision, ns, 0, d->base);
-        rc = run_steps(*d, key, nsteps - 1, st, [&](hipStream_t cs) {
-          return enqueue_stage_step(s, P, sh, precision, dt, pos, vel, ns, false, cs, nullptr);
-        });
-        if (rc) return rc;
-      }
+    if (!graph) {
+      for (int64_t k = 1; k < nsteps; ++k)
+        if ((rc = enqueue_stage_step(s, P, sh, precision, dt, pos, vel, ns, false, st, &tm)))
+          return rc;
+    } else {
+      const GraphKey key = graph_key(s, sh, dt, precision, ns, 0, d->base);
+      rc = run_steps(*d, key, nsteps, nsteps - 1, st, [&](hipStream_t cs) {
+        return enqueue_stage_step(s, P, sh, precision, dt, pos, vel, ns, false, cs, nullptr);
+      });
+      if (rc) return rc;
     }
     if ((rc = launch_stage(s, P, sh, precision, dt, pos, vel, 0, kStageFinal, ns, st))) return rc;
     if ((rc = tm.collect((double)(N - 1) * (double)(N - 2)))) return rc;
@@ -1607,12 +1608,10 @@ int pn_step(double* pos, double* vel, const double* mass, int64_t N, double G, d
       // the first sweep, nsteps - 1 steps (each ending in the next step's first
       // sweep), and the last step
       if ((rc = enqueue_rk4_head(s, P, sh, precision, dt, pos, vel, st, nullptr))) return rc;
-      if (nsteps > 1) {
-        rc = run_steps(*d, key, nsteps - 1, st, [&](hipStream_t cs) {
-          return enqueue_rk4_body(s, P, sh, precision, dt, pos, vel, true, cs, nullptr);
-        });
-        if (rc) return rc;
-      }
+      rc = run_steps(*d, key, nsteps, nsteps - 1, st, [&](hipStream_t cs) {
+        return enqueue_rk4_body(s, P, sh, precision, dt, pos, vel, true, cs, nullptr);
+      });
+      if (rc) return rc;
       if ((rc = enqueue_rk4_body(s, P, sh, precision, dt, pos, vel, false, st, nullptr)))
         return rc;
     }
@@ -1665,7 +1664,7 @@ int pn_step_hermite(double* pos, double* vel, const double* mass, int64_t N, dou
         if ((rc = enqueue_hermite_step(s, P, sh, dt, pos, vel, st))) return rc;
     } else {
       const GraphKey key = graph_key(s, sh, dt, PN_FP64, 0, 1, d->base);
-      rc = run_steps(*d, key, nsteps, st, [&](hipStream_t cs) {
+      rc = run_steps(*d, key, nsteps, nsteps, st, [&](hipStream_t cs) {
         return enqueue_hermite_step(s, P, sh, dt, pos, vel, cs);
       });
       if (rc) return rc;
@@ -1828,7 +1827,7 @@ int pn_step_batched(int32_t n_sys, const int64_t* offsets, const double* G, cons
   HIPCK(hipGetLastError());
   if (nsteps > 0) {
     const bool cached = d->bgexec && key == d->bkey;
-    d->basked_steps += nsteps;
+    if (graph) d->basked_steps += nsteps;
     if (graph && !cached && d->basked_steps >= kGraphAfterSteps) {
       drop_batch_graph(*d);
       HIPCK(hipStreamSynchronize(d->own));

@@ -6,6 +6,7 @@
 #include "pn_api.hip"
 
 #include <map>
+#include <memory>
 #include <set>
 #include <string>
 
@@ -201,6 +202,66 @@ void check_stage_shape() {
   }
 }
 
+// A system whose buffers no other system had (a graph may be cached for those).
+System& fresh(int64_t N) {
+  static std::vector<std::unique_ptr<System>> all;
+  all.push_back(std::make_unique<System>(N));
+  return *all.back();
+}
+
+// The entry points that step: one-launch and chained stages, Hermite, an ensemble.
+using Advance = int (*)(System&, int64_t nsteps, int flags, hipStream_t s);
+int hermite(System& a, int64_t nsteps, int flags, hipStream_t s) {
+  return pn_step_hermite(a.pos.data(), a.vel.data(), a.mass.data(), a.N, G, C, EPS, DT, nsteps, s,
+                         flags);
+}
+int rk4(System& a, int64_t nsteps, int flags, hipStream_t s) { return a.step(nsteps, flags, s); }
+int ensemble(System& a, int64_t nsteps, int flags, hipStream_t s) {
+  const int64_t offsets[3] = {0, a.N / 3, a.N};
+  const double g[2] = {G, G}, c[2] = {C, C}, eps[2] = {EPS, EPS};
+  return pn_step_batched(2, offsets, g, c, eps, a.pos.data(), a.vel.data(), a.mass.data(), DT,
+                         nsteps, PN_FP64, s, flags);
+}
+struct Scheme {
+  Advance run;
+  int64_t N, replay;  // bodies; steps of a call that can replay a graph
+};
+const Scheme kSchemes[] = {{rk4, 100, 17}, {rk4, 2500, 17}, {hermite, 150, 16}, {ensemble, 300, 1}};
+
+// A graph is captured by the first call that can replay it, once 256 steps in a
+// row were asked for by calls that allow graphs.
+void check_graph_count() {
+  EXPECT(pn_set_stage_kernel(PN_FP64, 2, 1000, 2) == PN_OK);
+  for (const Scheme& k : kSchemes) {
+    const auto captures = [&](std::initializer_list<std::pair<int64_t, int>> calls) {
+      System &a = fresh(k.N), &other = fresh(k.N);
+      EXPECT(k.run(other, 1, 0, nullptr) == PN_OK);  // (ends any count)
+      const Counts before = count;
+      for (const auto& c : calls) EXPECT(k.run(a, c.first, c.second, nullptr) == PN_OK);
+      const int n = count.captures - before.captures;
+      EXPECT((n > 0) == (count.replays > before.replays));
+      return n;
+    };
+    EXPECT(captures({{255, 0}}) == 0);
+    EXPECT(captures({{256, 0}}) == 1);
+    EXPECT(captures({{257, 0}}) == 1);
+    EXPECT(captures({{200, 0}, {55, 0}}) == 0);
+    EXPECT(captures({{200, 0}, {56, 0}}) == 1);
+    EXPECT(captures({{256, 0}, {40, 0}, {40, 0}}) == 1);
+    EXPECT(captures({{256, PN_NOGRAPH}, {100, 0}}) == 0);
+    EXPECT(captures({{200, 0}, {100, PN_NOGRAPH}, {55, 0}}) == 0);
+    EXPECT(captures({{255, 0}, {k.replay - 1, 0}}) == 0);
+    EXPECT(captures({{255, 0}, {k.replay, 0}}) == 1);
+    // a step per call
+    System& a = fresh(k.N);
+    const Counts before = count;
+    for (int i = 0; i < 300; ++i) EXPECT(k.run(a, 1, 0, nullptr) == PN_OK);
+    EXPECT(count.captures - before.captures == (k.replay > 1 ? 0 : 1));
+    EXPECT(k.run(a, k.replay, 0, nullptr) == PN_OK);
+    EXPECT(count.captures - before.captures == 1);
+  }
+}
+
 // pn_accel_noalloc allocates and frees nothing once the device is set up, by
 // whichever call: the first of all, and the first after pn_release.
 void check_noalloc() {
@@ -223,6 +284,7 @@ void check_noalloc() {
 
 int main(int argc, char** argv) {
   const std::map<std::string, void (*)()> checks = {
+      {"graph_count", check_graph_count},
       {"noalloc", check_noalloc},
       {"stage_shape", check_stage_shape},
   };
