@@ -35,7 +35,8 @@
  *   parameters, in one call or several (calls with PN_NOGRAPH or PN_TIMING do
  *   not count), by the first call that can replay it (at least 17 steps of
  *   pn_step, 16 of pn_step_hermite), and used for those pointers and parameters
- *   only; other steps are launched directly.
+ *   only; other steps are launched directly, as are all on a stream that the
+ *   caller is capturing.
  * - Return codes: PN_OK, or one of the negative codes below.  No C++ exception
  *   crosses the ABI.  Outputs are unspecified after an error, except
  *   PN_ENONFINITE, where all outputs are written.

@@ -1130,6 +1130,15 @@ GraphKey graph_key(const Sys& s, const Shape& sh, double dt, int precision, int 
   return key;
 }
 
+// Whether the caller is capturing `st`: its steps are then always launched
+// directly, whatever was asked for before, and become part of the caller's graph.
+int stream_capturing(hipStream_t st, bool* yes) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  HIPCK(hipStreamIsCapturing(st, &status));
+  *yes = status != hipStreamCaptureStatusNone;
+  return PN_OK;
+}
+
 // Captures `steps` time steps (on the library's own stream) into *graph/*exec.
 template <typename Enqueue>
 int capture_steps(DevState& d, int steps, Enqueue& enqueue_step, hipGraph_t* graph,
@@ -1163,19 +1172,21 @@ int capture_steps(DevState& d, int steps, Enqueue& enqueue_step, hipGraph_t* gra
 template <typename Enqueue>
 int run_steps(DevState& d, const GraphKey& key, int64_t asked, int64_t nsteps, hipStream_t st,
               Enqueue enqueue_step) {
-  int rc;
+  bool capturing;
+  int rc = stream_capturing(st, &capturing);
+  if (rc) return rc;
   if (!(key == d.asked)) {
     d.asked = key;
     d.asked_steps = 0;
   }
-  d.asked_steps += asked;
-  if (d.asked_steps >= kGraphAfterSteps && nsteps >= kStepsPerGraph && !(key == d.key)) {
+  if (!capturing) d.asked_steps += asked;
+  if (!capturing && d.asked_steps >= kGraphAfterSteps && nsteps >= kStepsPerGraph && !(key == d.key)) {
     drop_graph(d);
     if ((rc = capture_steps(d, kStepsPerGraph, enqueue_step, &d.graph, &d.gexec))) return rc;
     d.key = key;
   }
   int64_t k = 0;
-  if (key == d.key)
+  if (!capturing && key == d.key)
     for (; k + kStepsPerGraph <= nsteps; k += kStepsPerGraph) HIPCK(hipGraphLaunch(d.gexec, st));
   for (; k < nsteps; ++k)
     if ((rc = enqueue_step(st))) return rc;
@@ -1801,7 +1812,9 @@ int pn_step_batched(int32_t n_sys, const int64_t* offsets, const double* G, cons
   key.ipt = P.ipt;
   key.splits = P.splits;
   key.base = base;
-  const bool graph = !(flags & PN_NOGRAPH);
+  bool capturing;
+  if ((rc = stream_capturing(st, &capturing))) return rc;
+  const bool graph = !(flags & PN_NOGRAPH) && !capturing;
   // The descriptors in scratch are tracked apart from the cached graph: a
   // direct-launch call for another ensemble overwrites them while the graph
   // (captured for the first ensemble) stays cached.

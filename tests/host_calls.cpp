@@ -77,6 +77,10 @@ hipError_t hipStreamBeginCapture(hipStream_t s, hipStreamCaptureMode) {
   ++count.captures;
   return hipSuccess;
 }
+hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus* status) {
+  *status = capturing.count(s) ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+  return hipSuccess;
+}
 hipError_t hipStreamEndCapture(hipStream_t s, hipGraph_t* g) {
   EXPECT(capturing.count(s));
   *g = reinterpret_cast<hipGraph_t>(new Graph(capturing[s]));
@@ -262,6 +266,30 @@ void check_graph_count() {
   }
 }
 
+// Steps on a stream that the caller captures are launched directly, into the
+// caller's graph, however many were asked for before: no replay there, and no
+// capture of the library's own meanwhile.
+void check_caller_captures() {
+  hipStream_t s = static_cast<hipStream_t>(handle());
+  EXPECT(pn_set_stage_kernel(PN_FP64, 2, 1000, 2) == PN_OK);
+  for (const Scheme& k : kSchemes) {
+    for (const int64_t before : {2, 300}) {  // (300: a graph is cached)
+      System& a = fresh(k.N);
+      EXPECT(k.run(a, before, 0, s) == PN_OK);
+      const Counts c = count;
+      hipGraph_t g;
+      executed.clear();
+      EXPECT(hipStreamBeginCapture(s, hipStreamCaptureModeGlobal) == hipSuccess);
+      EXPECT(k.run(a, 300, PN_ASYNC, s) == PN_OK);
+      EXPECT(k.run(a, 300, PN_ASYNC, s) == PN_OK);
+      EXPECT(hipStreamEndCapture(s, &g) == hipSuccess);
+      EXPECT(count.captures == c.captures + 1 && count.replays == c.replays);
+      EXPECT(executed.empty() && reinterpret_cast<Graph*>(g)->size() >= 4 * 600);
+      EXPECT(hipGraphDestroy(g) == hipSuccess);
+    }
+  }
+}
+
 // pn_accel_noalloc allocates and frees nothing once the device is set up, by
 // whichever call: the first of all, and the first after pn_release.
 void check_noalloc() {
@@ -284,6 +312,7 @@ void check_noalloc() {
 
 int main(int argc, char** argv) {
   const std::map<std::string, void (*)()> checks = {
+      {"caller_captures", check_caller_captures},
       {"graph_count", check_graph_count},
       {"noalloc", check_noalloc},
       {"stage_shape", check_stage_shape},
