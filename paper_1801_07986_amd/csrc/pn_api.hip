@@ -1318,6 +1318,23 @@ BatchPlan plan_batch(int n_sys, const int64_t* off, int precision, const double*
   return P;
 }
 
+// Wavefronts per epilogue workgroup by their number: nine (the shortest) up to
+// one workgroup per CU, five up to two, four beyond, where throughput counts.  us
+// per step of FP64 ensembles with nine, five and four (and, mixed, the same):
+// 256 systems of 64 bodies 80.2, 80.5, 84.7 (72.1, 72.3, 76.0); 300 of 64 103.7,
+// 98.2, 101.4 (85.0, 80.0, 82.2); 64 of 500 (512 workgroups) 204.8, 199.9, 201.0;
+// 128 of 300 (640) 208.9, 205.2, 201.2; 1000 of 64 165.5, 161.8, 149.7 (130.2,
+// 126.8, 114.2); 3000 of 64 421.7, 382.8, 351.2 (318.1, 280.4, 250.0); 400 of 300
+// 494.4, 483.6, 456.1.
+void launch_epilogue_batched(const BatchArgs& b, int blocks, hipStream_t st) {
+  if (blocks <= kCUs)
+    hipLaunchKernelGGL(k_epilogue_batched<9>, dim3(blocks), dim3(64 * 9), 0, st, b);
+  else if (blocks <= 2 * kCUs)
+    hipLaunchKernelGGL(k_epilogue_batched<5>, dim3(blocks), dim3(64 * 5), 0, st, b);
+  else
+    hipLaunchKernelGGL(k_epilogue_batched<4>, dim3(blocks), dim3(64 * 4), 0, st, b);
+}
+
 int enqueue_batched_step(const BatchPlan& P, char* base, const double* mass, double* X, double* V,
                          double dt, int precision, hipStream_t st) {
   const int n_sys = (int)P.sys.size();
@@ -1363,7 +1380,7 @@ int enqueue_batched_step(const BatchPlan& P, char* base, const double* mass, dou
     }
     HIPCK(hipGetLastError());
     b.pre = pre_epi;
-    hipLaunchKernelGGL(k_epilogue_batched, dim3(P.pre_epi[n_sys]), dim3(epi_threads<double>()), 0, st, b);
+    launch_epilogue_batched(b, P.pre_epi[n_sys], st);
     HIPCK(hipGetLastError());
     hipLaunchKernelGGL(k_bh_final_batched, dim3(n_sys), dim3(kBlock), 0, st, b);
     HIPCK(hipGetLastError());

@@ -1187,14 +1187,18 @@ __device__ __forceinline__ void bh_quantities(const EpiArgs& a,
 }
 
 constexpr int kEpiStars = 64;  // stars per epilogue workgroup
-// Split ranges that an epilogue workgroup sums side by side (four wavefronts
-// each), the wavefronts that do so, and all its threads: one wavefront more
-// runs the epilogue.  (The dual epilogue's needs more than 168 registers per
-// lane, of which nine wavefronts fit a CU.)
+// Split ranges of an epilogue workgroup's sums and its wavefronts: four sum each
+// range, side by side, and one more runs the epilogue.  (The dual epilogue's needs
+// more than 168 registers per lane, of which nine wavefronts fit a CU: one range.)
+// With five the ranges are summed one after the other; with four, too, and the
+// last wavefront, which has the fewest fields, then runs the epilogue.  The sums
+// are the same.
 template <typename S>
 constexpr int epi_ranges() { return IsDual<S>::value ? 1 : 2; }
 template <typename S>
-constexpr int epi_threads() { return 64 * (4 * epi_ranges<S>() + 1); }
+constexpr int epi_waves() { return 4 * epi_ranges<S>() + 1; }
+template <typename S>
+constexpr int epi_threads() { return 64 * epi_waves<S>(); }
 template <typename S>
 constexpr int epi_fsum() { return kNF * Width<S>::n * kEpiStars * epi_ranges<S>(); }
 
@@ -1473,58 +1477,66 @@ __device__ __forceinline__ void epi_rows(const EpiArgs& a, int blk, const S (&bh
 // four wavefronts doing everything in turn, 8 splits at a time, an RK4 step
 // took 56.1 us instead of 50.9 at N = 1200, 142.0 instead of 137.3 at 4097
 // and 633 instead of 627 at 10001 (FP64).
-template <typename S, typename PkT = void>
+// Nine wavefronts fill a CU (126 registers per lane: sixteen fit), so they pay
+// while there is one workgroup per CU at most; ensembles have more, and take
+// fewer wavefronts per workgroup then (launch_epilogue_batched).
+template <typename S, typename PkT = void, int WAVES = epi_waves<S>()>
 __device__ __forceinline__ void epilogue_block(const EpiArgs& a, int blk, double* fsum) {
   constexpr bool DUAL = IsDual<S>::value;
   constexpr int W = DUAL ? 2 : 1;
   constexpr int NFO = kNF * W;
   constexpr int R = epi_ranges<S>();
   static_assert(kEpiStars == 64, "a star per lane");
+  static_assert(WAVES == 4 * R + 1 || WAVES == 5 || WAVES == 4, "wavefronts");
+  constexpr int SIDE = WAVES / 4;   // ranges summed side by side
+  constexpr int EPI = WAVES - 1;    // the wavefront that runs the epilogue
   const int wave = wave_id(), l = threadIdx.x & 63;
   const int k = blk * kEpiStars + l;
 
-  if (wave < 4 * R) {
+  if (wave < 4 * SIDE) {
     // split reduction: wavefront (h, g) sums fields g, g+4, g+8, ... over the
-    // splits of range h, in split order; the loads of up to 8 (dual: 4) splits
-    // of all its fields are issued together, then added in order
+    // splits of range h (and h + SIDE, ...), in split order; the loads of up to 8
+    // (dual: 4) splits of all its fields are issued together, then added in order
     constexpr int FPT = (NFO + 3) / 4;   // fields per thread
     constexpr int BATCH = DUAL ? 4 : 8;  // splits per batch of loads
-    const int g = wave & 3, h = wave >> 2;
+    const int g = wave & 3;
     const int per = (a.nsplit + R - 1) / R;
-    const int s0 = h * per, ns = min(a.nsplit - s0, per);
     if (k < a.Ns) {
       const size_t plane = (size_t)a.Ns;
       const size_t sstride = (size_t)NFO * plane;
-      double sum[FPT];
       bool use[FPT];
 #pragma unroll
-      for (int fi = 0; fi < FPT; ++fi) {
-        const int f = g + 4 * fi;
-        sum[fi] = 0.0;
-        use[fi] = f < NFO && epi_field_used(f, a);
-      }
-      const double* src = a.part + (size_t)g * plane + (size_t)s0 * sstride + k;
-      for (int sp = 0; sp < ns; sp += BATCH) {
-        double v[FPT][BATCH];
+      for (int fi = 0; fi < FPT; ++fi) use[fi] = g + 4 * fi < NFO && epi_field_used(g + 4 * fi, a);
+      for (int h = wave >> 2; h < R; h += SIDE) {
+        const int s0 = h * per, ns = min(a.nsplit - s0, per);
+        double sum[FPT];
+#pragma unroll
+        for (int fi = 0; fi < FPT; ++fi) sum[fi] = 0.0;
+        const double* src = a.part + (size_t)g * plane + (size_t)s0 * sstride + k;
+        for (int sp = 0; sp < ns; sp += BATCH) {
+          double v[FPT][BATCH];
+#pragma unroll
+          for (int fi = 0; fi < FPT; ++fi)
+#pragma unroll
+            for (int q = 0; q < BATCH; ++q)
+              v[fi][q] = (use[fi] && sp + q < ns)
+                             ? src[(size_t)4 * fi * plane + (size_t)(sp + q) * sstride]
+                             : 0.0;
+#pragma unroll
+          for (int fi = 0; fi < FPT; ++fi)
+#pragma unroll
+            for (int q = 0; q < BATCH; ++q)
+              if (sp + q < ns) sum[fi] += v[fi][q];
+        }
 #pragma unroll
         for (int fi = 0; fi < FPT; ++fi)
-#pragma unroll
-          for (int q = 0; q < BATCH; ++q)
-            v[fi][q] = (use[fi] && sp + q < ns)
-                           ? src[(size_t)4 * fi * plane + (size_t)(sp + q) * sstride]
-                           : 0.0;
-#pragma unroll
-        for (int fi = 0; fi < FPT; ++fi)
-#pragma unroll
-          for (int q = 0; q < BATCH; ++q)
-            if (sp + q < ns) sum[fi] += v[fi][q];
+          if (g + 4 * fi < NFO) fsum[(h * NFO + g + 4 * fi) * kEpiStars + l] = sum[fi];
       }
-#pragma unroll
-      for (int fi = 0; fi < FPT; ++fi)
-        if (g + 4 * fi < NFO) fsum[(h * NFO + g + 4 * fi) * kEpiStars + l] = sum[fi];
     }
-    __syncthreads();
-    return;
+    if (wave != EPI) {
+      __syncthreads();
+      return;
+    }
   }
 
   // the massive object and the stars' epilogue: every global read is requested
@@ -2639,11 +2651,12 @@ __global__ __launch_bounds__(kBlock) void k_pair_batched(BatchArgs b) {
   pair_block<T, MODE_FUSED, IPT, 4>(a, local % S.iblocks, local / S.iblocks, red);
 }
 
-__global__ __launch_bounds__(epi_threads<double>()) void k_epilogue_batched(BatchArgs b) {
+template <int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void k_epilogue_batched(BatchArgs b) {
   __shared__ double fsum[epi_fsum<double>()];
   const int r = batch_rank(b.pre, b.n_sys, blockIdx.x);
   const SysDev S = b.sys[b.order[r]];
-  epilogue_block<double>(batch_epi_args(b, S), blockIdx.x - b.pre[r], fsum);
+  epilogue_block<double, void, WAVES>(batch_epi_args(b, S), blockIdx.x - b.pre[r], fsum);
 }
 
 __global__ __launch_bounds__(kBlock) void k_bh_final_batched(BatchArgs b) {

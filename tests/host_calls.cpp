@@ -22,6 +22,7 @@
 struct Launch {
   std::string kernel;     // mangled name
   hipStream_t stream;     // where it was launched
+  unsigned blocks, threads;
   bool replayed = false;  // from a graph
   pn::StageArgs stage{};  // k_stage's argument
   pn::EpiArgs epi{};      // an epilogue's argument (k_epilogue..., k_stage_head)
@@ -59,8 +60,9 @@ hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* shmem, hipStream_
   *g = cfg_grid, *b = cfg_block, *shmem = cfg_shmem, *s = cfg_stream;
   return hipSuccess;
 }
-hipError_t hipLaunchKernel(const void* f, dim3, dim3, void** args, size_t, hipStream_t s) {
-  Launch l{names.at(f), s};
+hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, size_t,
+                           hipStream_t s) {
+  Launch l{names.at(f), s, grid.x, block.x};
   if (l.kernel.find("k_stage_head") != std::string::npos ||
       l.kernel.find("k_epilogue_chain") != std::string::npos)
     l.epi = *static_cast<pn::EpiArgs*>(args[0]);
@@ -290,6 +292,28 @@ void check_caller_captures() {
   }
 }
 
+// An ensemble's epilogue workgroups: as many as run side by side on a CU at 126
+// registers per lane (sixteen wavefronts) where there are more than one per CU.
+void check_ensemble_epilogues() {
+  for (const int systems : {1, 128, 129, 256, 257, 1000}) {  // of two workgroups each
+    System& a = fresh(101 * (int64_t)systems);
+    std::vector<int64_t> offsets;
+    for (int k = 0; k <= systems; ++k) offsets.push_back(101 * (int64_t)k);
+    const std::vector<double> g(systems, G), c(systems, C), eps(systems, EPS);
+    executed.clear();
+    EXPECT(pn_step_batched(systems, offsets.data(), g.data(), c.data(), eps.data(), a.pos.data(),
+                           a.vel.data(), a.mass.data(), DT, 1, PN_FP64, nullptr, 0) == PN_OK);
+    int found = 0;
+    for (const Launch& l : executed) {
+      if (l.kernel.find("k_epilogue_batched") == std::string::npos) continue;
+      ++found;
+      EXPECT(l.blocks == 2u * systems);
+      EXPECT(l.threads == (systems <= 128 ? 576u : systems <= 256 ? 320u : 256u));
+    }
+    EXPECT(found == 4);
+  }
+}
+
 // pn_accel_noalloc allocates and frees nothing once the device is set up, by
 // whichever call: the first of all, and the first after pn_release.
 void check_noalloc() {
@@ -313,6 +337,7 @@ void check_noalloc() {
 int main(int argc, char** argv) {
   const std::map<std::string, void (*)()> checks = {
       {"caller_captures", check_caller_captures},
+      {"ensemble_epilogues", check_ensemble_epilogues},
       {"graph_count", check_graph_count},
       {"noalloc", check_noalloc},
       {"stage_shape", check_stage_shape},

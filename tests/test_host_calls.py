@@ -28,7 +28,8 @@ def driver(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("check", ["stage_shape", "noalloc", "graph_count", "caller_captures"])
+@pytest.mark.parametrize("check", ["stage_shape", "noalloc", "graph_count", "caller_captures",
+                                   "ensemble_epilogues"])
 def test_host_calls(driver, check):
     env = {k: v for k, v in os.environ.items() if not k.startswith("PN_")}
     run = subprocess.run([driver, check], capture_output=True, text=True, timeout=120, env=env)
