@@ -30,11 +30,11 @@
  *   internal scratch, kept per device and grown on demand, and (pn_step) cached
  *   HIP graphs; pn_release() frees both.  No argument pointer is kept after the
  *   call returns, except inside the cached step graphs of pn_step,
- *   pn_step_hermite (16 steps per replay) and pn_step_batched.  A graph is
+ *   pn_step_hermite and pn_step_batched (16 steps per replay).  A graph is
  *   captured once 256 steps in a row were asked for with the same pointers and
  *   parameters, in one call or several (calls with PN_NOGRAPH or PN_TIMING do
  *   not count), by the first call that can replay it (at least 17 steps of
- *   pn_step, 16 of pn_step_hermite), and used for those pointers and parameters
+ *   pn_step, 16 of the others), and used for those pointers and parameters
  *   only; other steps are launched directly, as are all on a stream that the
  *   caller is capturing.
  * - Return codes: PN_OK, or one of the negative codes below.  No C++ exception

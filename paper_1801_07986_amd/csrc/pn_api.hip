@@ -318,27 +318,37 @@ struct BatchKey {
   }
 };
 
+// A cached graph of kStepsPerGraph time steps, and what it is for.
+template <typename Key>
+struct StepGraph {
+  hipGraph_t graph = nullptr;
+  hipGraphExec_t exec = nullptr;
+  Key key;    // what it was captured for
+  Key asked;  // what the last stepping call was for ...
+  int64_t asked_steps = 0;  // ... and the steps asked for in a row
+  void drop() {
+    if (exec) (void)hipGraphExecDestroy(exec);
+    if (graph) (void)hipGraphDestroy(graph);
+    exec = nullptr;
+    graph = nullptr;
+    key = Key();
+  }
+};
+
 struct DevState {
   bool init = false;
   hipStream_t own = nullptr;
   char* base = nullptr;
   size_t cap = 0;
   char* fixed = nullptr;  // this device's copy of `scratch` (pn_accel_noalloc)
-  hipGraph_t graph = nullptr;      // kStepsPerGraph time steps
-  hipGraphExec_t gexec = nullptr;
-  GraphKey key;    // the system the graph was captured for
-  GraphKey asked;  // the system of the last stepping call ...
-  int64_t asked_steps = 0;  // ... and its steps in a row
+  StepGraph<GraphKey> steps;
   std::vector<hipEvent_t> ev;
   // batched ensembles: own scratch and step graph
   char* bbase = nullptr;
   size_t bcap = 0;
-  hipGraph_t bgraph = nullptr;
-  hipGraphExec_t bgexec = nullptr;
-  BatchKey bkey;   // ensemble the cached graph was captured for
+  StepGraph<BatchKey> bsteps;
   BatchKey bdesc;  // ensemble whose descriptors are in the batched scratch now
   bool bdesc_valid = false;
-  int64_t basked_steps = 0;  // steps in a row of the ensemble in bdesc
   // every call's device work shares the scratch above: a call on another
   // stream than the previous one waits for it (last_ev recorded on last_st)
   hipEvent_t last_ev = nullptr;
@@ -380,26 +390,10 @@ int dev_state(DevState** out) {
   return PN_OK;
 }
 
-void drop_graph(DevState& d) {
-  if (d.gexec) (void)hipGraphExecDestroy(d.gexec);
-  if (d.graph) (void)hipGraphDestroy(d.graph);
-  d.gexec = nullptr;
-  d.graph = nullptr;
-  d.key = GraphKey();
-}
-
-void drop_batch_graph(DevState& d) {
-  if (d.bgexec) (void)hipGraphExecDestroy(d.bgexec);
-  if (d.bgraph) (void)hipGraphDestroy(d.bgraph);
-  d.bgexec = nullptr;
-  d.bgraph = nullptr;
-  d.bkey = BatchKey();
-}
-
 int ensure_batch_scratch(DevState& d, size_t bytes) {
   if (bytes <= d.bcap) return PN_OK;
   HIPCK(hipDeviceSynchronize());
-  drop_batch_graph(d);
+  d.bsteps.drop();
   d.bdesc_valid = false;
   if (d.bbase) HIPCK(hipFree(d.bbase));
   d.bbase = nullptr;
@@ -413,7 +407,7 @@ int ensure_batch_scratch(DevState& d, size_t bytes) {
 int ensure_scratch(DevState& d, size_t bytes) {
   if (bytes <= d.cap) return PN_OK;
   HIPCK(hipDeviceSynchronize());
-  drop_graph(d);  // graphs hold the old addresses
+  d.steps.drop();  // graphs hold the old addresses
   if (d.base) HIPCK(hipFree(d.base));
   d.base = nullptr;
   d.cap = 0;
@@ -1103,7 +1097,10 @@ constexpr int kStepsPerGraph = 16;
 // 230-350 us (N = 1024: 32 steps on new buffers 1856 us launched directly, 2099
 // with the capture; N = 3000, mixed, 8 steps: 774 and 1033), and replaying saves
 // at most 1.4 us a step (N = 1024: 52.0 against 53.4 us; N = 100: 36.1 and 36.3;
-// nothing from N = 10001 on, where the launches hide behind the sweeps).
+// nothing from N = 10001 on, where the launches hide behind the sweeps; small
+// ensembles 3 to 6 us a step: FP64, 2 systems of 64 bodies 65.5 us launched
+// directly, 62.7 replayed, 8 of 1000 133.3 and 130.2; a graph of one step took
+// 68.9 and 136.5; 1000 systems the same in both).
 constexpr int64_t kGraphAfterSteps = 256;
 
 // What a step graph was captured for: the caller's buffers and parameters, and
@@ -1169,25 +1166,26 @@ int capture_steps(DevState& d, int steps, Enqueue& enqueue_step, hipGraph_t* gra
 // (pn_step launches the first or last itself): by replays of the captured graph
 // where one is cached for this key or worth capturing, the rest directly.  The
 // steps and their order are the same, so are the results.
-template <typename Enqueue>
-int run_steps(DevState& d, const GraphKey& key, int64_t asked, int64_t nsteps, hipStream_t st,
-              Enqueue enqueue_step) {
+template <typename Key, typename Enqueue>
+int run_steps(DevState& d, StepGraph<Key>& g, const Key& key, int64_t asked, int64_t nsteps,
+              hipStream_t st, Enqueue enqueue_step) {
   bool capturing;
   int rc = stream_capturing(st, &capturing);
   if (rc) return rc;
-  if (!(key == d.asked)) {
-    d.asked = key;
-    d.asked_steps = 0;
+  if (!(key == g.asked)) {
+    g.asked = key;
+    g.asked_steps = 0;
   }
-  if (!capturing) d.asked_steps += asked;
-  if (!capturing && d.asked_steps >= kGraphAfterSteps && nsteps >= kStepsPerGraph && !(key == d.key)) {
-    drop_graph(d);
-    if ((rc = capture_steps(d, kStepsPerGraph, enqueue_step, &d.graph, &d.gexec))) return rc;
-    d.key = key;
+  if (!capturing) g.asked_steps += asked;
+  if (!capturing && g.asked_steps >= kGraphAfterSteps && nsteps >= kStepsPerGraph &&
+      !(key == g.key)) {
+    g.drop();
+    if ((rc = capture_steps(d, kStepsPerGraph, enqueue_step, &g.graph, &g.exec))) return rc;
+    g.key = key;
   }
   int64_t k = 0;
-  if (!capturing && key == d.key)
-    for (; k + kStepsPerGraph <= nsteps; k += kStepsPerGraph) HIPCK(hipGraphLaunch(d.gexec, st));
+  if (!capturing && key == g.key)
+    for (; k + kStepsPerGraph <= nsteps; k += kStepsPerGraph) HIPCK(hipGraphLaunch(g.exec, st));
   for (; k < nsteps; ++k)
     if ((rc = enqueue_step(st))) return rc;
   return PN_OK;
@@ -1613,7 +1611,7 @@ int pn_step(double* pos, double* vel, const double* mass, int64_t N, double G, d
           return rc;
     } else {
       const GraphKey key = graph_key(s, sh, dt, precision, ns, 0, d->base);
-      rc = run_steps(*d, key, nsteps, nsteps - 1, st, [&](hipStream_t cs) {
+      rc = run_steps(*d, d->steps, key, nsteps, nsteps - 1, st, [&](hipStream_t cs) {
         return enqueue_stage_step(s, P, sh, precision, dt, pos, vel, ns, false, cs, nullptr);
       });
       if (rc) return rc;
@@ -1636,7 +1634,7 @@ int pn_step(double* pos, double* vel, const double* mass, int64_t N, double G, d
       // the first sweep, nsteps - 1 steps (each ending in the next step's first
       // sweep), and the last step
       if ((rc = enqueue_rk4_head(s, P, sh, precision, dt, pos, vel, st, nullptr))) return rc;
-      rc = run_steps(*d, key, nsteps, nsteps - 1, st, [&](hipStream_t cs) {
+      rc = run_steps(*d, d->steps, key, nsteps, nsteps - 1, st, [&](hipStream_t cs) {
         return enqueue_rk4_body(s, P, sh, precision, dt, pos, vel, true, cs, nullptr);
       });
       if (rc) return rc;
@@ -1692,7 +1690,7 @@ int pn_step_hermite(double* pos, double* vel, const double* mass, int64_t N, dou
         if ((rc = enqueue_hermite_step(s, P, sh, dt, pos, vel, st))) return rc;
     } else {
       const GraphKey key = graph_key(s, sh, dt, PN_FP64, 0, 1, d->base);
-      rc = run_steps(*d, key, nsteps, nsteps, st, [&](hipStream_t cs) {
+      rc = run_steps(*d, d->steps, key, nsteps, nsteps, st, [&](hipStream_t cs) {
         return enqueue_hermite_step(s, P, sh, dt, pos, vel, cs);
       });
       if (rc) return rc;
@@ -1829,9 +1827,6 @@ int pn_step_batched(int32_t n_sys, const int64_t* offsets, const double* G, cons
   key.ipt = P.ipt;
   key.splits = P.splits;
   key.base = base;
-  bool capturing;
-  if ((rc = stream_capturing(st, &capturing))) return rc;
-  const bool graph = !(flags & PN_NOGRAPH) && !capturing;
   // The descriptors in scratch are tracked apart from the cached graph: a
   // direct-launch call for another ensemble overwrites them while the graph
   // (captured for the first ensemble) stays cached.
@@ -1850,35 +1845,18 @@ int pn_step_batched(int32_t n_sys, const int64_t* offsets, const double* G, cons
     HIPCK(hipStreamSynchronize(st));
     d->bdesc = key;
     d->bdesc_valid = true;
-    d->basked_steps = 0;
   }
   if (!(flags & PN_ASYNC) && (rc = take_host(*d))) return rc;
   hipLaunchKernelGGL(k_reset_status, dim3(1), dim3(64), 0, st, status);
   HIPCK(hipGetLastError());
-  if (nsteps > 0) {
-    const bool cached = d->bgexec && key == d->bkey;
-    if (graph) d->basked_steps += nsteps;
-    if (graph && !cached && d->basked_steps >= kGraphAfterSteps) {
-      drop_batch_graph(*d);
-      HIPCK(hipStreamSynchronize(d->own));
-      HIPCK(hipStreamBeginCapture(d->own, hipStreamCaptureModeThreadLocal));
-      rc = enqueue_batched_step(P, base, mass, pos, vel, dt, precision, d->own);
-      hipGraph_t g = nullptr;
-      hipError_t e = hipStreamEndCapture(d->own, &g);
-      if (rc) {
-        if (g) (void)hipGraphDestroy(g);
-        return rc;
-      }
-      if (e != hipSuccess) return fail_hip(e, "hipStreamEndCapture", __LINE__);
-      d->bgraph = g;
-      HIPCK(hipGraphInstantiate(&d->bgexec, d->bgraph, nullptr, nullptr, 0));
-      d->bkey = key;
-    }
-    const bool replay = graph && d->bgexec && key == d->bkey;
-    for (int64_t k = 0; k < nsteps; ++k) {
-      if (replay) HIPCK(hipGraphLaunch(d->bgexec, st));
-      else if ((rc = enqueue_batched_step(P, base, mass, pos, vel, dt, precision, st))) return rc;
-    }
+  const auto enqueue = [&](hipStream_t cs) {
+    return enqueue_batched_step(P, base, mass, pos, vel, dt, precision, cs);
+  };
+  if (flags & PN_NOGRAPH) {
+    for (int64_t k = 0; k < nsteps; ++k)
+      if ((rc = enqueue(st))) return rc;
+  } else if (nsteps > 0) {
+    if ((rc = run_steps(*d, d->bsteps, key, nsteps, nsteps, st, enqueue))) return rc;
   }
   if ((rc = mark_call_end(*d, st))) return rc;
   if (flags & PN_ASYNC) return PN_OK;
@@ -1992,8 +1970,8 @@ int pn_release(void) {
     if (!d.init) continue;
     (void)hipSetDevice((int)dev);
     (void)hipDeviceSynchronize();
-    drop_graph(d);
-    drop_batch_graph(d);
+    d.steps.drop();
+    d.bsteps.drop();
     if (d.bbase) (void)hipFree(d.bbase);
     d.bbase = nullptr;
     d.bcap = 0;

@@ -232,7 +232,7 @@ struct Scheme {
   Advance run;
   int64_t N, replay;  // bodies; steps of a call that can replay a graph
 };
-const Scheme kSchemes[] = {{rk4, 100, 17}, {rk4, 2500, 17}, {hermite, 150, 16}, {ensemble, 300, 1}};
+const Scheme kSchemes[] = {{rk4, 100, 17}, {rk4, 2500, 17}, {hermite, 150, 16}, {ensemble, 300, 16}};
 
 // A graph is captured by the first call that can replay it, once 256 steps in a
 // row were asked for by calls that allow graphs.
@@ -262,9 +262,11 @@ void check_graph_count() {
     System& a = fresh(k.N);
     const Counts before = count;
     for (int i = 0; i < 300; ++i) EXPECT(k.run(a, 1, 0, nullptr) == PN_OK);
-    EXPECT(count.captures - before.captures == (k.replay > 1 ? 0 : 1));
+    EXPECT(count.captures - before.captures == 0);
     EXPECT(k.run(a, k.replay, 0, nullptr) == PN_OK);
-    EXPECT(count.captures - before.captures == 1);
+    EXPECT(count.captures - before.captures == 1 && count.replays - before.replays == 1);
+    EXPECT(k.run(a, k.replay + 16 * 9 + 15, 0, nullptr) == PN_OK);  // 16 steps per replay
+    EXPECT(count.captures - before.captures == 1 && count.replays - before.replays == 11);
   }
 }
 
