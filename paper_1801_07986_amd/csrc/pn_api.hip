@@ -678,8 +678,12 @@ void launch_pair_bh_t(const PairArgs& a, const EpiArgs& e, const Shape& sh, hipS
   // not add to the largest share of a CU: an i-block's workgroups then run on the
   // XCD of the epilogue workgroup that reads their sums and writes their next
   // packets (N = 3000 mixed 76.9 instead of 81.8 us per RK4 step, FP64 93.9
-  // instead of 97.9).  Two: one column more than a multiple of 64 (N = 16384 FP64
-  // 1489 instead of 1525: the splits of an i-block would all run on one XCD).
+  // instead of 97.9; 6000 mixed 177 instead of 183; one column more is never
+  // better).  Two: one column more than a multiple of 64, by measurement alone
+  // (FP64, i-blocks: us with and without it: 128 1499, 1511; 192 3289, 3314; 256
+  // 5798, 5818; 320 8945, 9008).  At other multiples of eight it gains 0.8 % at
+  // most (160 2306, 2324; 224 4446, 4470) and costs up to 8 % (144 2056, 1908; 176
+  // 2969, 2806).
   int gx = sh.iblocks % 64 == 0 ? sh.iblocks + 1 : sh.iblocks;
   if (sh.ipt == 1) {
     const auto share = [&](int64_t cols) { return (cols * sh.nsplit + kCUs - 1) / kCUs; };

@@ -1816,7 +1816,9 @@ __device__ __forceinline__ void stage_bh_update(const StageArgs& sa, const doubl
 }
 
 // epi_star_load of a Runge-Kutta stage, without a branch: every load in flight
-// together (the stage sums, too, where a stage has none yet).
+// together (the stage sums, too, where a stage has none yet).  Lanes beyond the
+// workgroup's stars load stars of other workgroups, which may be storing them at
+// that moment; those lanes' values are never used.
 __device__ __forceinline__ EpiStar<double> stage_star_load(const EpiArgs& a, int k) {
   const size_t i = (size_t)k + 1;
   const double* ub = a.ub + 4 * (size_t)k;
