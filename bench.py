@@ -51,11 +51,22 @@ PEAK_FP32_VALU = 157.3e12
 # Keyed by (workload, kernel, j-splits): the launch shape comes from the tuned
 # table, so a figure applies only to the kernel and split count it was taken on.
 TRAFFIC_BYTES = {
-    # FETCH 7288.77 KiB, WRITE 17291.1 KiB per launch
-    ("plummer_n16384_fp64", "k_pair_bh<double,3,2,8>", 12): 32633487,
-    # FETCH 49328.6 KiB, WRITE 94334.7 KiB per launch
-    ("plummer_n65536_mixed", "k_pair_bh<float,3,1,8>", 16): 197623706,
+    # FETCH 6507.9 KiB, WRITE 23054.7 KiB per launch
+    ("plummer_n16384_fp64", "k_pair_bh<double,3,2,8>", 16): 36936192,
+    # FETCH 30777.1 KiB, WRITE 94334.7 KiB per launch
+    ("plummer_n65536_mixed", "k_pair_bh<float,3,1,8>", 16): 159630233,
 }
+
+
+def sweep_kernel(pn, prec: int, N: int):
+    """The kernel that pn_step times with PN_TIMING, and its j-splits: the sweep
+    of the chained stages, or the one-launch stage of a small system."""
+    T = "double" if prec == pn.PN_FP64 else "float"
+    ns = pn.pn_query_stage_kernel(prec, N)
+    if ns > 0:
+        return f"k_stage<{T},{ns},{'true' if N - 1 <= 512 // ns else 'false'}>", 1
+    ipt, ws, nsplit, _ = pn.pn_query_shape(prec, N)
+    return f"k_pair_bh<{T},3,{ipt},{ws}>", nsplit
 
 
 def log(msg: str) -> None:
@@ -150,7 +161,8 @@ def main() -> int:
     # dominant kernel: the fused pair sweep, timed per launch with HIP events
     # on the stream it runs on (direct launches, same kernels and shapes).  In
     # RK4 steps every sweep but a call's first is k_pair_bh (the sweep plus
-    # one workgroup doing the previous stage's massive-object update)
+    # one workgroup doing the previous stage's massive-object update); small
+    # systems run their stages in one launch, which is timed as a whole
     tsteps = max(2, min(25, args.steps))
     pn.pn_step(pos, vel, mass, G, c, eps, dt, tsteps, prec, stream=stream, flags=pn.PN_TIMING)
     tm = pn.pn_last_timing()
@@ -158,8 +170,7 @@ def main() -> int:
     flops = FLOP_PER_PAIR_FUSED * tm["pairs_per_launch"]
     achieved = flops / avg_s
     peak = PEAK_FP64_VALU if prec == pn.PN_FP64 else PEAK_FP32_VALU
-    ipt, ws, nsplit, _ = pn.pn_query_shape(prec, N)
-    kname = f"k_pair_bh<{'double' if prec == pn.PN_FP64 else 'float'},3,{ipt},{ws}>"
+    kname, nsplit = sweep_kernel(pn, prec, N)
     traffic = TRAFFIC_BYTES.get((args.workload, kname, nsplit))
     roofline = {"bound": "alu", "achieved": achieved / 1e12, "peak": peak / 1e12,
                 "unit": "TFLOP/s", "frac": achieved / peak, "traffic": traffic,

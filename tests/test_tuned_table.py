@@ -38,3 +38,19 @@ def test_stage_rows_hold_a_win(table):
     """The autotuner's margin between the two forms: 3 %."""
     for e in table["stage"]:
         assert e["step_ms"] <= 0.97 * e["chain_step_ms"], e
+
+
+def test_bench_knows_the_timed_kernels(lib):
+    """bench.py's measured HBM traffic is for the kernels and split counts that the
+    table selects, and a small system's kernel is the one-launch stage."""
+    import os
+    import sys
+
+    sys.path.insert(0, os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
+    import bench
+
+    for name, prec, N in (("plummer_n16384_fp64", FP64, 16384),
+                          ("plummer_n65536_mixed", MIXED, 65536)):
+        assert (name, *bench.sweep_kernel(lib, prec, N)) in bench.TRAFFIC_BYTES
+    assert bench.sweep_kernel(lib, FP64, 1024) == ("k_stage<double,4,false>", 1)
+    assert bench.sweep_kernel(lib, FP64, 100) == ("k_stage<double,2,true>", 1)
