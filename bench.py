@@ -142,7 +142,7 @@ def main() -> int:
     mass = torch.from_numpy(mass0).to(dev)
     stream = torch.cuda.current_stream()
 
-    # warmup (also captures the step graph)
+    # warmup (the step graph is captured by the timed run, from 256 steps on)
     pn.pn_step(pos, vel, mass, G, c, eps, dt, args.warmup, prec, stream=stream)
     torch.cuda.synchronize()
     log("warmup done")
@@ -485,7 +485,7 @@ def table32(pn, torch, inputs, samples, with_cpu, oracle_budget_s=40.0):
             pn.pn_step(pos, vel, mass, 1.0, 1.0, 1e-3, dt, 32, pn.PN_FP64)
             e1 = pn.pn_diagnostics(pos, vel, mass, 1.0, 1.0, 1e-3)
             t = time.perf_counter() - t0
-            if k > 0:  # the first run captures the step graph
+            if k > 0:  # the first run is a warm-up
                 times.append(t)
         row = {"N": N, "gpu_mean_s": float(np.mean(times)), "gpu_std_s": float(np.std(times)),
                "energy_rel_change": abs((e1[0] + e1[1]) - (e0[0] + e0[1])) / abs(e0[0] + e0[1]),

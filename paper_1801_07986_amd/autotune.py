@@ -1,7 +1,7 @@
 """Launch-shape autotuner for the star-star sweep.
 
 For each precision and a ladder of system sizes it times whole RK4 steps
-(pn_step: the chained sequence of sweeps and epilogues, replayed as a graph;
+(pn_step: the chained sequence of sweeps and epilogues, long runs replayed as a graph;
 wall clock around a run of steps on the caller's stream) over the candidate
 shapes
 
@@ -63,7 +63,7 @@ def candidates(N: int):
 
 def time_step(pn, torch, P, V, Mm, prec, budget_s=0.05, reps=3):
     """Best of `reps` runs of whole RK4 steps (each run at least budget_s of
-    wall clock); ms per step.  The first call captures the step graph."""
+    wall clock); ms per step."""
     stream = torch.cuda.current_stream()
     pn.pn_step(P, V, Mm, 1.0, 30.0, 1e-4, 1e-7, 2, prec, stream=stream)
     torch.cuda.synchronize()
@@ -158,7 +158,7 @@ def tune_batched(log=print, steps=2, reps=2):
         timings = {}
         for ipt, ns in BATCH_CANDIDATES:
             os.environ["PN_BATCH_SHAPE"] = f"{ipt},{ns}"
-            pn.pn_step_batched(off, Gs, cs, es, P, V, Mm, 1e-7, 1, prec)  # captures the graph
+            pn.pn_step_batched(off, Gs, cs, es, P, V, Mm, 1e-7, 1, prec)  # warm-up
             torch.cuda.synchronize()
             best = None
             for _ in range(reps):

@@ -1097,14 +1097,14 @@ constexpr int kStepsPerGraph = 16;
 // one set of buffers and parameters (in one call or several that allow graphs;
 // every step a caller asks for counts), by the first call that has steps enough
 // to replay it; until then, and for steps left over, the kernels are launched
-// directly.  Capturing takes
-// 230-350 us (N = 1024: 32 steps on new buffers 1856 us launched directly, 2099
-// with the capture; N = 3000, mixed, 8 steps: 774 and 1033), and replaying saves
-// at most 1.4 us a step (N = 1024: 52.0 against 53.4 us; N = 100: 36.1 and 36.3;
-// nothing from N = 10001 on, where the launches hide behind the sweeps; small
-// ensembles 3 to 6 us a step: FP64, 2 systems of 64 bodies 65.5 us launched
-// directly, 62.7 replayed, 8 of 1000 133.3 and 130.2; a graph of one step took
-// 68.9 and 136.5; 1000 systems the same in both).
+// directly.  Capturing takes 230-350 us (32 steps of two kernels per stage on new
+// buffers 1856 us launched directly, 2099 with the capture), and replaying saves
+// at most 1.2 us a step (N = 64 22.2 us launched directly, 21.5 replayed; 3000,
+// mixed, 77.5 and 76.3; Hermite N = 1000 37.2 and 36.3; nothing at 300 to 2049
+// and from 10001 on), in small ensembles 3 to 6 (FP64, 2 systems of 64 bodies
+// 65.5 and 62.7, 8 of 1000 133.3 and 130.2; a graph of one step took 68.9 and
+// 136.5; 1000 systems the same in both).  A first run of 273 steps on new buffers
+// takes no longer with its capture than without (N = 1024 8973 and 9017 us).
 constexpr int64_t kGraphAfterSteps = 256;
 
 // What a step graph was captured for: the caller's buffers and parameters, and
