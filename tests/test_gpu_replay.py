@@ -149,3 +149,28 @@ def test_two_streams(pn, kind, N, prec):
         _advance(pn, kind, prec, b, n, pn.PN_ASYNC, sb)
     torch.cuda.synchronize()
     assert _equal(a, alone[0]) and _equal(b, alone[1])
+
+
+@pytest.mark.parametrize("kind,N,prec", KINDS)
+def test_caller_captures_steps(pn, kind, N, prec):
+    """Asynchronous steps on a stream that the caller captures go into the caller's
+    graph, also when the library has a graph of its own for them: three replays,
+    with eager work and a synchronisation after each, equal three direct calls."""
+    S, D = _dev(N, 68), _dev(N, 68)
+    s = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for T, flags in ((D, pn.PN_NOGRAPH), (S, 0)):  # (S last: its graph is cached, and an
+        _advance(pn, kind, prec, T, 300, flags, s)  # ensemble's descriptors are in place)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        _advance(pn, kind, prec, S, 40, pn.PN_ASYNC, s)
+    for _ in range(3):
+        g.replay()
+        torch.cuda.synchronize()
+        assert float((S[0] * S[0]).sum()) > 0.0
+    assert torch.isfinite(S[0]).all()
+    for _ in range(3):
+        _advance(pn, kind, prec, D, 40, pn.PN_NOGRAPH, s)
+    torch.cuda.synchronize()
+    assert _equal(S, D)
